@@ -202,7 +202,9 @@ ccs_status ccs_intersect(const ccs_scene* scene, const ccs_ray* rays, uint32_t n
  * splits), backtracks, Gregory bound recomputations (Alg. 2, including each
  * Gregory candidate's root), leaf records, Bezier grid re-crops after
  * backtracking (Alg. 1), Gregory candidates.  A separately compiled copy of the
- * same kernel; used for measurement. */
+ * same kernel that keeps every ray on one lane to its end (ccs_intersect spreads
+ * the rays of a small launch, and a launch's last ones, over 16 lanes each, with
+ * the same hits); used for measurement. */
 ccs_status ccs_intersect_counted(const ccs_scene* scene, const ccs_ray* rays, uint32_t n, ccs_hit* hits,
                                  uint32_t* counters, void* stream);
 

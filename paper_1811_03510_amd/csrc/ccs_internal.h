@@ -60,7 +60,8 @@ struct BatchTable {
 // the launch's ray-queue counter.
 struct LaunchParams {
   uint32_t fetch_min, traverse_min, grid_min, traverse_steps, decide_min;
-  uint32_t* queue;
+  uint32_t* queue;  // nullptr inside the kernel: the rays are taken by position, one per lane
+  uint32_t lanes;   // lanes of a wave that take rays (set by launch_intersect)
 };
 
 // BVH depth the learned variant's node stack holds (its LDS also holds a 64-byte
@@ -75,7 +76,7 @@ constexpr uint32_t kMaxBvhDepthLearned = 32;
 // CCS_MAX_LEAF_DEPTH) with 64-bit codes, closest-first order only.
 constexpr uint32_t kMaxLeafDepth32 = 16;
 int max_waves_per_cu(bool counted, bool learned, bool single_box, bool deep);
-hipError_t launch_intersect(const DeviceScene& s, const BatchTable& bt, uint32_t* counters, const LaunchParams& lp,
+hipError_t launch_intersect(const DeviceScene& s, const BatchTable& bt, uint32_t* counters, LaunchParams lp,
                             uint32_t waves_per_cu, hipStream_t stream);
 hipError_t launch_refit(const DeviceScene& s, const float* cp_world, const uint32_t* level_offsets,
                         uint32_t n_levels, hipStream_t stream);

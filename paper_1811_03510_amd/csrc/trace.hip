@@ -17,6 +17,11 @@
 // expensive, divergent phases run on well-filled waves.  Which lane holds which
 // ray, and when, never changes a ray's result.
 //
+// A launch's last rays are few and long (the heaviest of 460k takes 2600 steps and
+// recomputes, the mean is 40): once the queue is empty and a wave holds at most
+// kTailRays of them, it spreads each over 16 lanes (trace_group.h), and launches of
+// few rays run that way from the start (k_trace_wide).  Bits are the same.
+//
 // Alg. 3 state per lane (registers only, no stack):
 //   code  interleaved path bits of the current domain; split k (u at even k)
 //         owns bit 2L-1-k and is set when the upper half was taken;
@@ -36,10 +41,17 @@
 #include "patch_math.h"
 #include "policy.h"
 #include "ray_valid.h"
+#include "trace_group.h"
 
 namespace ccs {
 
 constexpr int kBlock = 64;
+// Once the queue is empty a wave keeps one ray per lane until this many are left and
+// then gives each 16 lanes (trace_group.h).  Measured on a field of 200 objects in
+// world frames (460k rays), 16 animation frames of the torus and a two-bounce path
+// at 1280x720: 4, 8, 12, 16 and 21 give the same times within their spread (at 4
+// the torus' 32k rays take 6 % longer), 0 takes 1.3 to 1.5 times as long.
+constexpr int kTailRays = 12;
 constexpr uint32_t kGridOwners = kBlock / 3;  // lanes whose grids one recompute phase serves
 
 enum Mode : int { kFetch = 0, kTraverse = 1, kStep = 2, kGrid = 3, kDead = 4, kDecide = 5 };
@@ -98,10 +110,74 @@ __device__ __forceinline__ void write_hit(const BatchTable& bt, uint32_t* __rest
 // enters the lower half with the upper one pending; a missed box backtracks, and
 // a hit leaf box is recorded at its own entry distance.  No distance orders the
 // halves, and every pending half costs a grid recompute.
+
+// Runs a wave's groups until every one is dead.  next(want) gives the groups whose
+// lanes are set in `want` a ray each, or ends them.
+template <int kStride, typename CodeT, typename Next>
+__device__ __forceinline__ void group_loop(GroupRay<CodeT>& r, const GroupLane& ln, const BatchTable& bt, int L2,
+                                           float leaf_scale, int lane, int*& stack, Next next) {
+  auto finish = [&]() {
+    if ((lane & (kGroupLanes - 1)) == 0) {
+      const Counts none = {0, 0, 0, 0, 0, 0, 0, 0};
+      write_hit<false>(bt, nullptr, r.rid, r.best_t, r.best_id, r.hu, r.hv, none);
+    }
+    r.mode = kGroupFree;
+  };
+  for (;;) {
+    const uint64_t want = __ballot(r.mode == kGroupFree);
+    if (want != 0) next(want);
+    if (__ballot(r.mode != kGroupDead) == 0) break;
+    if (r.mode == kGroupWalk) {
+      for (int it = 0; it < kGroupNodeSteps && r.mode == kGroupWalk; ++it) {
+        if (r.cur < 0)
+          group_candidate(r, ln);
+        else if (!group_node<kStride>(r, ln, stack))
+          finish();
+      }
+    }
+    if (r.mode == kGroupGrid) group_grid(r, ln);
+    if (r.mode == kGroupStep) {
+      if (!group_step(r, ln, L2, leaf_scale)) {
+        if (r.sp > 0) {
+          --r.sp;
+          r.cur = stack[r.sp * kStride];
+          r.mode = kGroupWalk;
+        } else {
+          finish();
+        }
+      }
+    }
+  }
+}
+
+// A group's ray of the launch: its two words, its frame's nodes, records and frames.
+template <typename CodeT>
+__device__ __forceinline__ void group_open_ray(GroupRay<CodeT>& r, const GroupLane& ln, const DeviceScene& s,
+                                               const BatchTable& bt, float4& ro, float4& rd) {
+  const ccs_ray* rays = bt.rays[0];
+  uint32_t local = r.rid, frame = bt.frame[0];
+  for (uint32_t q = 1; q < bt.n_batches; ++q)
+    if (r.rid >= bt.prefix[q]) {
+      rays = bt.rays[q];
+      local = r.rid - bt.prefix[q];
+      frame = bt.frame[q];
+    }
+  const float4* r4 = reinterpret_cast<const float4*>(rays + local);
+  ro = r4[0];
+  rd = r4[1];
+  r.nodes = s.nodes + (size_t)frame * s.frame_node_f4;
+  r.recs = s.recs + (size_t)frame * s.frame_rec_floats;
+  r.frames = s.frames ? s.frames + (size_t)frame * s.frame_frames_f4 : nullptr;
+  group_set_ray(r, ln, ro, rd);
+}
+
 template <bool kStats, bool kLearned, bool kSingle, typename CodeT>
-__device__ __forceinline__ void trace_body(DeviceScene s, BatchTable bt, uint32_t* __restrict__ counters,
-                                           LaunchParams lp) {
+__device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTable& bt, uint32_t* __restrict__ counters,
+                                           const LaunchParams& lp) {
   constexpr int kStack = kLearned ? (int)kMaxBvhDepthLearned : (int)kMaxBvhDepth;
+  constexpr bool kTail = !kStats && !kLearned && !kSingle && kTailRays > 0;
+  uint64_t busy = 0;      // lanes that hold a ray
+  bool drained = false;   // the queue is known to be empty
   __shared__ int stack[kStack * kBlock];
   // learned order, 16 words per lane: the node's corners and slab results from the
   // split until the decision, then the network's inputs, then its logits; and the
@@ -115,7 +191,7 @@ __device__ __forceinline__ void trace_body(DeviceScene s, BatchTable bt, uint32_
   const float leaf_scale = __uint_as_float((uint32_t)(127 - s.leaf_depth) << 23);  // 2^-L
 
   const uint32_t n = bt.prefix[bt.n_batches];
-  int mode = kFetch;
+  int mode = kLearned || (uint32_t)lane < lp.lanes ? kFetch : kDead;
   uint32_t rid = 0;
   const float4* nodes = s.nodes;  // the current ray's frame
   const float* recs = s.recs;
@@ -137,12 +213,17 @@ __device__ __forceinline__ void trace_body(DeviceScene s, BatchTable bt, uint32_
   float pix = 0.0f, piy = 0.0f, piz = 0.0f;  // reciprocal direction in the current patch's frame
 
   for (;;) {
-    if (__ballot(mode != kDead) == 0) break;
     uint64_t mf = __ballot(mode == kFetch);
     uint64_t mt = __ballot(mode == kTraverse);
     uint64_t ms = __ballot(mode == kStep);
     uint64_t mg = __ballot(mode == kGrid);
     if (kLearned) ms |= __ballot(mode == kDecide);  // lanes that will step once decided
+    if (kTail) {
+      busy = mt | ms | mg;
+      if (drained && __popcll(busy) <= kTailRays) break;
+    } else if ((mf | mt | ms | mg) == 0) {
+      break;
+    }
 
     // Wave priority: a wave in the fetch or traversal phase is about to wait on a
     // chain of dependent loads (queue atomic and ray, or node after node), so it
@@ -151,10 +232,16 @@ __device__ __forceinline__ void trace_body(DeviceScene s, BatchTable bt, uint32_
     __builtin_amdgcn_s_setprio(1);
     // ------------------------------------------------------------ fetch rays
     if (mf != 0 && ((uint32_t)__popcll(mf) >= lp.fetch_min || (mt | ms | mg) == 0)) {
-      const int leader = __ffsll((unsigned long long)mf) - 1;
       uint32_t base = 0;
-      if (lane == leader) base = atomicAdd(lp.queue, (uint32_t)__popcll(mf));
-      base = __shfl(base, leader);
+      if (!kLearned && lp.queue == nullptr) {  // one fetch per wave takes the whole launch
+        base = drained ? n : blockIdx.x * lp.lanes;
+        drained = true;
+      } else {
+        const int leader = __ffsll((unsigned long long)mf) - 1;
+        if (lane == leader) base = atomicAdd(lp.queue, (uint32_t)__popcll(mf));
+        base = __shfl(base, leader);
+        drained = base + (uint32_t)__popcll(mf) >= n;
+      }
       if (mode == kFetch) {
         rid = base + (uint32_t)__popcll(mf & ((1ull << lane) - 1ull));
         if (rid >= n) {
@@ -522,6 +609,132 @@ __device__ __forceinline__ void trace_body(DeviceScene s, BatchTable bt, uint32_
       }
     }
   }
+  // The wave's last rays, 16 lanes each (trace_group.h).  Their states go through
+  // the node stack's columns of lanes that hold no ray, two columns of kStack words
+  // a ray; a ray's own column is its node stack as before.
+  if constexpr (kTail) {
+    static_assert(kStack >= 48 && 3 * kTailRays <= 64, "two free columns per ray");
+    if (busy == 0) return;
+    __builtin_amdgcn_s_setprio(2);
+    if ((busy >> lane) & 1ull) {
+      const uint32_t k = (uint32_t)__popcll(busy & ((1ull << lane) - 1ull));
+      int* c0 = stack + nth_set_bit(~busy, 2 * k);
+      int* c1 = stack + nth_set_bit(~busy, 2 * k + 1);
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          c0[(4 * a + b) * kBlock] = __float_as_int(G.x[a][b]);
+          c0[(16 + 4 * a + b) * kBlock] = __float_as_int(G.y[a][b]);
+          c0[(32 + 4 * a + b) * kBlock] = __float_as_int(G.z[a][b]);
+        }
+      const uint32_t words[25] = {(uint32_t)mode, (uint32_t)cur, (uint32_t)sp, rid, rec_idx, pmeta,
+                                  (uint32_t)code, (uint32_t)((uint64_t)code >> 32), (uint32_t)trail,
+                                  (uint32_t)((uint64_t)trail >> 32), (uint32_t)depth | (mirror << 8),
+                                  bits(pox), bits(poy), bits(poz), bits(pix), bits(piy), bits(piz),
+                                  bits(dx), bits(dy), bits(dz), bits(ptmin), bits(pt0), bits(best_t), best_id,
+                                  bits(pad2)};
+#pragma unroll
+      for (int k2 = 0; k2 < 25; ++k2) c1[k2 * kBlock] = (int)words[k2];
+    }
+    __syncthreads();
+    const GroupLane ln(lane);
+    GroupRay<CodeT> r;
+    r.mode = kGroupFree;
+    r.rid = 0;
+    int* column = stack;
+    uint32_t taken = 0;
+    const uint32_t n_live = (uint32_t)__popcll(busy);
+    group_loop<kBlock>(r, ln, bt, L2, leaf_scale, lane, column, [&](uint64_t want) {
+      const uint32_t k = taken + (uint32_t)__popcll(want & ((1ull << (lane & ~(kGroupLanes - 1))) - 1ull)) / kGroupLanes;
+      taken += (uint32_t)__popcll(want) / kGroupLanes;
+      if (r.mode != kGroupFree) return;
+      if (k >= n_live) {
+        r.mode = kGroupDead;
+        return;
+      }
+      const uint32_t owner = nth_set_bit(busy, k);
+      const int* c0 = stack + nth_set_bit(~busy, 2 * k);
+      const int* c1 = stack + nth_set_bit(~busy, 2 * k + 1);
+      column = stack + owner;
+      auto f = [&](int w) { return __int_as_float(c1[w * kBlock]); };
+      const int m = c1[0];
+      r.mode = m == kTraverse ? kGroupWalk : m == kStep ? kGroupStep : kGroupGrid;
+      r.cur = c1[1 * kBlock];
+      r.sp = c1[2 * kBlock];
+      r.rid = (uint32_t)c1[3 * kBlock];
+      r.rec_idx = (uint32_t)c1[4 * kBlock];
+      r.pmeta = (uint32_t)c1[5 * kBlock];
+      r.code = (CodeT)(((uint64_t)(uint32_t)c1[7 * kBlock] << 32) | (uint32_t)c1[6 * kBlock]);
+      r.trail = (CodeT)(((uint64_t)(uint32_t)c1[9 * kBlock] << 32) | (uint32_t)c1[8 * kBlock]);
+      r.depth = c1[10 * kBlock] & 0xFF;
+      r.mirror = (uint32_t)c1[10 * kBlock] >> 8;
+      r.po = f(11 + ln.c);
+      r.pi = f(14 + ln.c);
+      r.dd = f(17 + ln.c);
+      r.ptmin = f(20);
+      r.pt0 = f(21);
+      r.best_t = f(22);
+      r.best_id = (uint32_t)c1[23 * kBlock];
+      r.pad2 = f(24);
+      r.hu = s_uv[0][owner];
+      r.hv = s_uv[1][owner];
+#pragma unroll
+      for (int a = 0; a < 4; ++a) r.g[a] = __int_as_float(c0[(16 * ln.c + 4 * a + ln.b) * kBlock]);
+      float4 ro, rd;
+      group_open_ray(r, ln, s, bt, ro, rd);
+      group_corner(r, leaf_scale);
+      if (r.mode != kGroupWalk) group_load_record(r, ln);
+    });
+  }
+}
+
+// Small launches: every ray on 16 lanes from the start, `groups` (1, 2 or 4) rays to
+// a wave, all of them in flight at once.  Bound by the heaviest ray's chain of
+// steps: 0.27 us per split and 0.67 us per recompute (375 instructions at one per 6
+// cycles, all that one wave issues) against 0.87 us for either on one lane.
+// 1024 rays of the torus: 270 -> 87 us; 16384 secondary rays: 621 -> 275 us.
+template <typename CodeT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_trace_wide(DeviceScene s,
+                                                                                              BatchTable bt,
+                                                                                              uint32_t groups) {
+  __shared__ int stack[kMaxBvhDepth * kGroupsPerWave];
+  const int lane = threadIdx.x;
+  const uint32_t n = bt.prefix[bt.n_batches];
+  const int L2 = 2 * s.leaf_depth;
+  const float leaf_scale = __uint_as_float((uint32_t)(127 - s.leaf_depth) << 23);
+  const GroupLane ln(lane);
+  const uint32_t group = (uint32_t)lane / kGroupLanes;
+  GroupRay<CodeT> r;
+  r.rid = blockIdx.x * groups + group;
+  r.mode = group < groups && r.rid < n ? kGroupFree : kGroupDead;
+  bool first = true;
+  int* column = stack + group;
+  group_loop<kGroupsPerWave>(r, ln, bt, L2, leaf_scale, lane, column, [&](uint64_t) {
+    const bool open = first;
+    first = false;
+    if (r.mode != kGroupFree) return;
+    if (!open) {
+      r.mode = kGroupDead;
+      return;
+    }
+    float4 ro, rd;
+    group_open_ray(r, ln, s, bt, ro, rd);
+    r.best_t = rd.w;
+    r.best_id = kNoHit;
+    r.hu = r.hv = 0.0f;
+    r.cur = 0;
+    r.sp = 0;
+    if (ray_traced(ro, rd) && s.n_nodes > 0) {
+      r.mode = kGroupWalk;
+    } else {
+      if ((lane & (kGroupLanes - 1)) == 0) {
+        const Counts none = {0, 0, 0, 0, 0, 0, 0, 0};
+        write_hit<false>(bt, nullptr, r.rid, r.best_t, r.best_id, 0.0f, 0.0f, none);
+      }
+      r.mode = kGroupDead;
+    }
+  });
 }
 
 template <bool kStats, bool kLearned>
@@ -665,19 +878,69 @@ int max_waves_per_cu(bool counted, bool learned, bool single_box, bool deep) {
   return counted ? resident_waves_per_cu<true, false, false, false>() : resident_waves_per_cu<false, false, false, false>();
 }
 
-hipError_t launch_intersect(const DeviceScene& s, const BatchTable& bt, uint32_t* counters, const LaunchParams& lp,
+template <typename CodeT>
+static int wide_waves_per_cu() {
+  static const int per_cu = [] {
+    int v = 0;
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k_trace_wide<CodeT>, kBlock, 0);
+    return std::max(1, v);
+  }();
+  return per_cu;
+}
+
+// Launches of at most this many rays per compute unit (16384 on 256) take
+// k_trace_wide.  Per-ray work is about three times the one-lane kernel's, so it
+// loses once the machine is full: 16384 / 24000 / 32768 secondary rays of the torus
+// take 275 / 363 / 485 us against 374 / 363 / 366 us with one ray per lane, of 200
+// objects 331 / 484 / 570 against 503 / 548 / 552 us, and in world frames
+// 725 / 1311 / 1533 against 932 / 1512 / 1726 us.
+constexpr uint32_t kWideRaysPerCu = 64;
+
+// Fewest lanes of a wave that take rays in a launch that all lanes could hold at
+// once, and the waves per compute unit over which it is spread before lanes are
+// filled: 32k rays of the torus take 300 us at 16 lanes on 2048 waves against 342
+// (24 lanes) and 390 us (64 lanes, 512 waves); 12 lanes on 2731 waves are no faster
+// there and 3 % slower on a path's 184k-ray level.
+constexpr uint32_t kMinLanes = 16, kSpreadWavesPerCu = 8;
+
+hipError_t launch_intersect(const DeviceScene& s, const BatchTable& bt, uint32_t* counters, LaunchParams lp,
                             uint32_t waves_per_cu, hipStream_t stream) {
   const uint32_t n = bt.prefix[bt.n_batches];
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(1), 0, stream, lp.queue);
   // the host refuses the learned order and the single-box ablation above kMaxLeafDepth32
   const bool deep = s.leaf_depth > (int)kMaxLeafDepth32;
   const bool learned = s.policy.w != nullptr && !s.single_box && !deep;
   int per_cu = max_waves_per_cu(counters != nullptr, learned, s.single_box && !deep, deep);
   if (waves_per_cu > 0) per_cu = std::min(per_cu, (int)waves_per_cu);
   const uint32_t waves = (uint32_t)(per_cu * s.n_cus);
-  const uint32_t needed = (n + kBlock - 1) / kBlock;
-  const dim3 grid(std::min(waves, needed)), block(kBlock);
+  const dim3 block(kBlock);
+  if (!counters && !learned && !s.single_box && n <= kWideRaysPerCu * s.n_cus) {
+    int wide = deep ? wide_waves_per_cu<uint64_t>() : wide_waves_per_cu<uint32_t>();
+    if (waves_per_cu > 0) wide = std::min(wide, (int)waves_per_cu);
+    const uint32_t room = (uint32_t)wide * s.n_cus;
+    if (n <= kGroupsPerWave * room) {  // always, but under a small waves_per_cu
+      const uint32_t groups = n <= room ? 1u : n <= 2u * room ? 2u : 4u;
+      const dim3 grid((n + groups - 1) / groups);
+      if (deep)
+        hipLaunchKernelGGL(k_trace_wide<uint64_t>, grid, block, 0, stream, s, bt, groups);
+      else
+        hipLaunchKernelGGL(k_trace_wide<uint32_t>, grid, block, 0, stream, s, bt, groups);
+      return hipGetLastError();
+    }
+  }
+  // rays that all fit are taken by position, without the queue (the learned variant, at its
+  // register limit, keeps the queue)
+  uint32_t n_waves = std::min(waves, (n + kBlock - 1) / kBlock);
+  if (!learned && n <= waves * kBlock) {
+    const uint32_t spread = std::min(waves, kSpreadWavesPerCu * s.n_cus);
+    lp.lanes = std::min((uint32_t)kBlock, std::max(kMinLanes, std::max((n + waves - 1) / waves, (n + spread - 1) / spread)));
+    lp.queue = nullptr;
+    n_waves = (n + lp.lanes - 1) / lp.lanes;
+  } else {
+    lp.lanes = kBlock;
+    hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(1), 0, stream, lp.queue);
+  }
+  const dim3 grid(n_waves);
   if (deep) {
     if (counters)
       hipLaunchKernelGGL(HIP_KERNEL_NAME(k_trace_deep<true>), grid, block, 0, stream, s, bt, counters, lp);
