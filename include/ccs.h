@@ -258,8 +258,8 @@ ccs_status ccs_bounce_frame(const ccs_scene* scene, uint32_t frame, const ccs_ra
  * to out_rays[0, m) in their input order, writes the input index of out_rays[k]
  * to out_index[k], and m to work[0].  Every other ray would be returned as a miss
  * by an intersection entry point.  `work` is caller-owned device memory of
- * CCS_COMPACT_WORK_WORDS(n) uint32 (word 0 the count, the rest the scan's
- * per-block counts); the library allocates nothing, so calls with different
+ * CCS_COMPACT_WORK_WORDS(n) uint32 (word 0 the count, the rest counts of runs
+ * of rays); the library allocates nothing, so calls with different
  * `work` buffers may run concurrently.  All pointers are device pointers; out_rays
  * and out_index hold up to n elements and may not alias rays.  Asynchronous on
  * `stream`: read m after the stream has reached the call.  n = 0 sets work[0] = 0. */
