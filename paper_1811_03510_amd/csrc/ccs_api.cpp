@@ -90,7 +90,7 @@ struct ccs_scene {
   float lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
   double build_seconds = 0.0;
   float* cp_stage = nullptr;  // device staging buffer for host refit input
-  std::vector<uint32_t> level_offsets;  // nodes of depth d: level_nodes[level_offsets[d] .. level_offsets[d+1])
+  std::vector<ccs::RefitPass> refit_passes;
   uint32_t* queues = nullptr;  // kQueueSlots ray-queue counters
   std::atomic<uint32_t> next_queue{0};
   ccs_launch_params launch{0, 16, 1, 8, 3, 8};
@@ -332,31 +332,23 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
   D.leaf_depth = (int)desc->leaf_depth;
   D.single_box = (desc->flags & CCS_FLAG_SINGLE_BOX) != 0;
   float4* nodes = nullptr;
-  uint32_t *perm = nullptr, *invp = nullptr, *lvl = nullptr;
-  int32_t *lpar = nullptr, *npar = nullptr;
+  uint32_t *perm = nullptr, *invp = nullptr, *blk_i = nullptr, *blk_n = nullptr, *nid = nullptr;
+  int32_t *lpar = nullptr, *npar = nullptr, *iup = nullptr, *islot = nullptr, *nup = nullptr;
+  const ccs::RefitPlan plan = ccs::plan_refit(bvh.nodes, bvh.leaf_parent, bvh.node_parent, ccs::kRefitCap0, ccs::kRefitCap1);
+  s->refit_passes = plan.passes;
   float* drec = nullptr;
   if ((st = dev_alloc(s, &nodes, (size_t)n_nodes * 4)) != CCS_OK || (st = dev_alloc(s, &drec, recs.size())) != CCS_OK ||
       (st = dev_alloc(s, &perm, n)) != CCS_OK || (st = dev_alloc(s, &invp, n)) != CCS_OK ||
       (st = dev_alloc(s, &lpar, n)) != CCS_OK || (st = dev_alloc(s, &npar, n_nodes)) != CCS_OK ||
-      (st = dev_alloc(s, &lvl, n_nodes)) != CCS_OK || (st = dev_alloc(s, &s->queues, kQueueSlots)) != CCS_OK) {
+      (st = dev_alloc(s, &blk_i, plan.block_items.size())) != CCS_OK ||
+      (st = dev_alloc(s, &blk_n, plan.block_nodes.size())) != CCS_OK ||
+      (st = dev_alloc(s, &iup, plan.item_up.size())) != CCS_OK ||
+      (st = dev_alloc(s, &islot, plan.item_slot.size())) != CCS_OK ||
+      (st = dev_alloc(s, &nid, plan.node_id.size())) != CCS_OK ||
+      (st = dev_alloc(s, &nup, plan.node_up.size())) != CCS_OK ||
+      (st = dev_alloc(s, &s->queues, kQueueSlots)) != CCS_OK) {
     free_scene(s);
     return st;
-  }
-  // nodes grouped by depth for the level-by-level refit (parents precede children
-  // in the depth-first layout, so one pass gives every depth)
-  std::vector<uint32_t> node_depth(n_nodes, 0), level_nodes(n_nodes);
-  uint32_t max_d = 0;
-  for (uint32_t k = 1; k < n_nodes; ++k) {
-    const int32_t link = bvh.node_parent[k];
-    node_depth[k] = link < 0 ? 0 : node_depth[(uint32_t)link >> 1] + 1;
-    max_d = std::max(max_d, node_depth[k]);
-  }
-  s->level_offsets.assign(n_nodes ? max_d + 2 : 1, 0);
-  for (uint32_t k = 0; k < n_nodes; ++k) s->level_offsets[node_depth[k] + 1]++;
-  for (size_t d = 1; d < s->level_offsets.size(); ++d) s->level_offsets[d] += s->level_offsets[d - 1];
-  {
-    std::vector<uint32_t> fill(s->level_offsets.begin(), s->level_offsets.end() - 1);
-    for (uint32_t k = 0; k < n_nodes; ++k) level_nodes[fill[node_depth[k]]++] = k;
   }
   hipStream_t stream = (hipStream_t)desc->stream;
   struct Up {
@@ -369,7 +361,12 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
              {invp, inv_perm.data(), (size_t)n * 4},
              {lpar, bvh.leaf_parent.data(), (size_t)n * 4},
              {npar, bvh.node_parent.data(), (size_t)n_nodes * 4},
-             {lvl, level_nodes.data(), (size_t)n_nodes * 4}};
+             {blk_i, plan.block_items.data(), plan.block_items.size() * 4},
+             {blk_n, plan.block_nodes.data(), plan.block_nodes.size() * 4},
+             {iup, plan.item_up.data(), plan.item_up.size() * 4},
+             {islot, plan.item_slot.data(), plan.item_slot.size() * 4},
+             {nid, plan.node_id.data(), plan.node_id.size() * 4},
+             {nup, plan.node_up.data(), plan.node_up.size() * 4}};
   for (const Up& u : ups) {
     if (u.bytes == 0) continue;
     e = hipMemcpyAsync(u.dst, u.src, u.bytes, hipMemcpyHostToDevice, stream);
@@ -389,7 +386,7 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
   D.inv_perm = invp;
   D.leaf_parent = lpar;
   D.node_parent = npar;
-  D.level_nodes = lvl;
+  D.refit = ccs::RefitDev{blk_i, blk_n, nid, iup, islot, nup};
   int cus = 0;
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) {
@@ -499,7 +496,7 @@ ccs_status ccs_refit_frame(ccs_scene* s, uint32_t frame, const float* control_po
   f.recs = s->dev.recs + frame * s->dev.frame_rec_floats;
   f.nodes = s->dev.nodes + frame * s->dev.frame_node_f4;
   if (f.frames) f.frames = s->dev.frames + frame * s->dev.frame_frames_f4;
-  hipError_t e = ccs::launch_refit(f, src, s->level_offsets.data(), (uint32_t)s->level_offsets.size() - 1, st);
+  hipError_t e = ccs::launch_refit(f, src, s->refit_passes, st);
   if (e != hipSuccess) return hip_fail(e, "refit launch");
   // host input goes through the scene's one staging buffer: wait until the refit has
   // read it, so that a refit on another stream cannot overwrite it meanwhile

@@ -4,7 +4,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/ccs.h"
+#include "refit_plan.h"
 
 namespace ccs {
 
@@ -15,6 +18,14 @@ struct PolicyDev {
   const uint2* w;   // kPolicyWTiles * 64 lanes x 4 bfloat16
   const float4* b;  // kPolicyBTiles * 64 lanes x 4 fp32
 };
+
+// The refit plan's arrays on the device (refit_plan.h).
+struct RefitDev {
+  const uint32_t *block_items, *block_nodes, *node_id;
+  const int32_t *item_up, *item_slot, *node_up;
+};
+// Records of a workgroup of the refit's first pass (4 lanes each), items of one of the later passes.
+constexpr uint32_t kRefitCap0 = 64, kRefitCap1 = 1024;
 
 // BVH node: 64 bytes = 4 float4.
 //   f[0] = (lo0.x, lo0.y, lo0.z, hi0.x)
@@ -32,7 +43,7 @@ struct DeviceScene {
   const uint32_t* inv_perm;  // original index -> record
   const int32_t* leaf_parent;  // record -> (node << 1 | side)
   const int32_t* node_parent;  // node -> (parent << 1 | side), -1 for the root
-  const uint32_t* level_nodes;  // node indices sorted by depth (refit order; offsets on the host)
+  RefitDev refit;              // the refit's work plan (refit_plan.h)
   uint32_t n_cus;            // compute units of the device
   uint32_t n_frames;         // frames: copies of recs and node boxes sharing one topology
   size_t frame_rec_floats;   // floats per frame in recs (n_patches * kRecFloats)
@@ -78,8 +89,8 @@ constexpr uint32_t kMaxLeafDepth32 = 16;
 int max_waves_per_cu(bool counted, bool learned, bool single_box, bool deep);
 hipError_t launch_intersect(const DeviceScene& s, const BatchTable& bt, uint32_t* counters, LaunchParams lp,
                             uint32_t waves_per_cu, hipStream_t stream);
-hipError_t launch_refit(const DeviceScene& s, const float* cp_world, const uint32_t* level_offsets,
-                        uint32_t n_levels, hipStream_t stream);
+hipError_t launch_refit(const DeviceScene& s, const float* cp_world, const std::vector<RefitPass>& passes,
+                        hipStream_t stream);
 hipError_t launch_policy_pack(const float* params, uint2* w, float4* b, hipStream_t stream);
 hipError_t launch_policy_infer(const PolicyDev& P, const float* x, uint32_t n, float* z, hipStream_t stream);
 hipError_t launch_record(const DeviceScene& s, const ccs_ray* rays, const ccs_hit* hits, uint32_t n, float* feats,

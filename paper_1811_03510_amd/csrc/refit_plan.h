@@ -1,0 +1,43 @@
+// Work plan of the BVH refit: which workgroup unions which node boxes, in a few
+// passes instead of one launch per level.
+//
+// Pass 0 covers the patch records: every maximal subtree of at most `cap0` records
+// is a treelet, consecutive treelets share a workgroup's `cap0` places (70 % of them
+// filled on the object fields; taking subtrees apart to fill 90 % made the first pass
+// no faster and the second one slower), and a record whose parent lies above every
+// treelet only fills its slot.  The treelets'
+// root slots and those records are the items of pass 1, whose treelets hold at most
+// `cap1` items, and so on until one treelet holds the root.  Inside a workgroup a
+// thread starts at its item and climbs: the second child to arrive at a node unions
+// the two boxes and goes on, the first one stops.
+#pragma once
+
+#include <cstdint>
+#include <vector>
+
+namespace ccs {
+
+// Slots and links are (node << 1 | side).
+struct RefitPass {
+  uint32_t first_block = 0, n_blocks = 0;  // in block_items / block_nodes
+};
+
+struct RefitPlan {
+  std::vector<RefitPass> passes;
+  // per block, and one end value after each pass's last block
+  std::vector<uint32_t> block_items;  // first item: a record (pass 0) or an index into item_slot / item_up
+  std::vector<uint32_t> block_nodes;  // first entry of node_id / node_up
+  std::vector<int32_t> item_up;       // item -> link to its parent among the block's nodes, -1: outside the block
+  std::vector<int32_t> item_slot;     // item -> the slot that holds its box (records: their slot)
+  std::vector<uint32_t> node_id;      // node of a block -> node of the BVH
+  std::vector<int32_t> node_up;       // node of a block -> link to its parent in the block, -1: a treelet's root
+};
+
+// nodes: 16 floats per node, the children's references as bits at 12 and 13 (>= 0
+// node, < 0 record ~child), in depth-first order (left child = node + 1); leaf_parent
+// and node_parent as the builder gives them.  Items of pass 0 come in record order,
+// so item k < leaf_parent.size() is record k.
+RefitPlan plan_refit(const std::vector<float>& nodes, const std::vector<int32_t>& leaf_parent,
+                     const std::vector<int32_t>& node_parent, uint32_t cap0, uint32_t cap1);
+
+}  // namespace ccs
