@@ -113,9 +113,11 @@ __device__ __forceinline__ void write_hit(const BatchTable& bt, uint32_t* __rest
 
 // Runs a wave's groups until every one is dead.  next(want) gives the groups whose
 // lanes are set in `want` a ray each, or ends them.
-template <int kStride, typename CodeT, typename Next>
-__device__ __forceinline__ void group_loop(GroupRay<CodeT>& r, const GroupLane& ln, const BatchTable& bt, int L2,
-                                           float leaf_scale, int lane, int*& stack, Next next) {
+template <int kStride, bool kLearned, typename CodeT, typename Next>
+__device__ __forceinline__ void group_loop(GroupRay<CodeT>& r, const GroupLane& ln, const BatchTable& bt,
+                                           const PolicyDev& policy, uint32_t* feats, int L2, float leaf_scale, int lane,
+                                           int*& stack, Next next) {
+  uint32_t mirror0 = 0;  // learned order: mirror bits of the node that waits for the network
   auto finish = [&]() {
     if ((lane & (kGroupLanes - 1)) == 0) {
       const Counts none = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -137,7 +139,7 @@ __device__ __forceinline__ void group_loop(GroupRay<CodeT>& r, const GroupLane& 
     }
     if (r.mode == kGroupGrid) group_grid(r, ln);
     if (r.mode == kGroupStep) {
-      if (!group_step(r, ln, L2, leaf_scale)) {
+      if (!group_step<kLearned>(r, ln, L2, leaf_scale, feats + 16 * (lane / kGroupLanes), mirror0)) {
         if (r.sp > 0) {
           --r.sp;
           r.cur = stack[r.sp * kStride];
@@ -147,6 +149,7 @@ __device__ __forceinline__ void group_loop(GroupRay<CodeT>& r, const GroupLane& 
         }
       }
     }
+    if (kLearned) group_decide(r, policy, feats, mirror0, L2, lane, leaf_scale);
   }
 }
 
@@ -175,9 +178,10 @@ template <bool kStats, bool kLearned, bool kSingle, typename CodeT>
 __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTable& bt, uint32_t* __restrict__ counters,
                                            const LaunchParams& lp) {
   constexpr int kStack = kLearned ? (int)kMaxBvhDepthLearned : (int)kMaxBvhDepth;
-  constexpr bool kTail = !kStats && !kLearned && !kSingle && kTailRays > 0;
+  constexpr bool kTail = !kStats && !kSingle;
   uint64_t busy = 0;      // lanes that hold a ray
   bool drained = false;   // the queue is known to be empty
+  bool few = false;       // and few enough rays are left to spread them
   __shared__ int stack[kStack * kBlock];
   // learned order, 16 words per lane: the node's corners and slab results from the
   // split until the decision, then the network's inputs, then its logits; and the
@@ -220,7 +224,9 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
     if (kLearned) ms |= __ballot(mode == kDecide);  // lanes that will step once decided
     if (kTail) {
       busy = mt | ms | mg;
-      if (drained && __popcll(busy) <= kTailRays) break;
+      few = drained && __popcll(busy) <= kTailRays;
+      // learned order: not while a node waits for the network with its values in LDS
+      if (few && (!kLearned || __ballot(mode == kDecide) == 0)) break;
     } else if ((mf | mt | ms | mg) == 0) {
       break;
     }
@@ -444,7 +450,7 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
     if (kLearned) {
       const uint64_t md = __ballot(mode == kDecide);
       const uint32_t n_dec = (uint32_t)__popcll(md);
-      if (md != 0 && (n_dec >= lp.decide_min || __ballot(mode == kStep) == 0)) {
+      if (md != 0 && (few || n_dec >= lp.decide_min || __ballot(mode == kStep) == 0)) {
         // deciding lanes take consecutive slots, so the network runs on ceil(n / 16)
         // column tiles instead of every tile holding one of them (all slot reads of
         // the node values precede the first input store in the wave's program order)
@@ -610,32 +616,35 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
     }
   }
   // The wave's last rays, 16 lanes each (trace_group.h).  Their states go through
-  // the node stack's columns of lanes that hold no ray, two columns of kStack words
+  // the node stack's columns of lanes that hold no ray, kCols columns of kStack words
   // a ray; a ray's own column is its node stack as before.
   if constexpr (kTail) {
-    static_assert(kStack >= 48 && 3 * kTailRays <= 64, "two free columns per ray");
+    constexpr int kWords = 48 + 26, kCols = (kWords + kStack - 1) / kStack;
+    static_assert((kCols + 1) * kTailRays <= kBlock, "free columns for every ray's words");
     if (busy == 0) return;
     __builtin_amdgcn_s_setprio(2);
     if ((busy >> lane) & 1ull) {
       const uint32_t k = (uint32_t)__popcll(busy & ((1ull << lane) - 1ull));
-      int* c0 = stack + nth_set_bit(~busy, 2 * k);
-      int* c1 = stack + nth_set_bit(~busy, 2 * k + 1);
+      int* col[kCols];
+#pragma unroll
+      for (int c = 0; c < kCols; ++c) col[c] = stack + nth_set_bit(~busy, kCols * k + c);
+      auto put = [&](int w, uint32_t v) { col[w / kStack][(w % kStack) * kBlock] = (int)v; };
 #pragma unroll
       for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-          c0[(4 * a + b) * kBlock] = __float_as_int(G.x[a][b]);
-          c0[(16 + 4 * a + b) * kBlock] = __float_as_int(G.y[a][b]);
-          c0[(32 + 4 * a + b) * kBlock] = __float_as_int(G.z[a][b]);
+          put(4 * a + b, bits(G.x[a][b]));
+          put(16 + 4 * a + b, bits(G.y[a][b]));
+          put(32 + 4 * a + b, bits(G.z[a][b]));
         }
-      const uint32_t words[25] = {(uint32_t)mode, (uint32_t)cur, (uint32_t)sp, rid, rec_idx, pmeta,
+      const uint32_t words[26] = {(uint32_t)mode, (uint32_t)cur, (uint32_t)sp, rid, rec_idx, pmeta,
                                   (uint32_t)code, (uint32_t)((uint64_t)code >> 32), (uint32_t)trail,
                                   (uint32_t)((uint64_t)trail >> 32), (uint32_t)depth | (mirror << 8),
                                   bits(pox), bits(poy), bits(poz), bits(pix), bits(piy), bits(piz),
                                   bits(dx), bits(dy), bits(dz), bits(ptmin), bits(pt0), bits(best_t), best_id,
-                                  bits(pad2)};
+                                  bits(pad2), vpref};
 #pragma unroll
-      for (int k2 = 0; k2 < 25; ++k2) c1[k2 * kBlock] = (int)words[k2];
+      for (int w = 0; w < 26; ++w) put(48 + w, words[w]);
     }
     __syncthreads();
     const GroupLane ln(lane);
@@ -645,7 +654,7 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
     int* column = stack;
     uint32_t taken = 0;
     const uint32_t n_live = (uint32_t)__popcll(busy);
-    group_loop<kBlock>(r, ln, bt, L2, leaf_scale, lane, column, [&](uint64_t want) {
+    group_loop<kBlock, kLearned>(r, ln, bt, s.policy, s_feat, L2, leaf_scale, lane, column, [&](uint64_t want) {
       const uint32_t k = taken + (uint32_t)__popcll(want & ((1ull << (lane & ~(kGroupLanes - 1))) - 1ull)) / kGroupLanes;
       taken += (uint32_t)__popcll(want) / kGroupLanes;
       if (r.mode != kGroupFree) return;
@@ -654,33 +663,41 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
         return;
       }
       const uint32_t owner = nth_set_bit(busy, k);
-      const int* c0 = stack + nth_set_bit(~busy, 2 * k);
-      const int* c1 = stack + nth_set_bit(~busy, 2 * k + 1);
+      const int* col[kCols];
+#pragma unroll
+      for (int c = 0; c < kCols; ++c) col[c] = stack + nth_set_bit(~busy, kCols * k + c);
       column = stack + owner;
-      auto f = [&](int w) { return __int_as_float(c1[w * kBlock]); };
-      const int m = c1[0];
+      auto get = [&](int w) {  // w differs between lanes: the column is picked by selects
+        const int* c = col[0];
+#pragma unroll
+        for (int q = 1; q < kCols; ++q) c = w / kStack == q ? col[q] : c;
+        return (uint32_t)c[(w % kStack) * kBlock];
+      };
+      auto getf = [&](int w) { return __uint_as_float(get(w)); };
+      const int m = (int)get(48);
       r.mode = m == kTraverse ? kGroupWalk : m == kStep ? kGroupStep : kGroupGrid;
-      r.cur = c1[1 * kBlock];
-      r.sp = c1[2 * kBlock];
-      r.rid = (uint32_t)c1[3 * kBlock];
-      r.rec_idx = (uint32_t)c1[4 * kBlock];
-      r.pmeta = (uint32_t)c1[5 * kBlock];
-      r.code = (CodeT)(((uint64_t)(uint32_t)c1[7 * kBlock] << 32) | (uint32_t)c1[6 * kBlock]);
-      r.trail = (CodeT)(((uint64_t)(uint32_t)c1[9 * kBlock] << 32) | (uint32_t)c1[8 * kBlock]);
-      r.depth = c1[10 * kBlock] & 0xFF;
-      r.mirror = (uint32_t)c1[10 * kBlock] >> 8;
-      r.po = f(11 + ln.c);
-      r.pi = f(14 + ln.c);
-      r.dd = f(17 + ln.c);
-      r.ptmin = f(20);
-      r.pt0 = f(21);
-      r.best_t = f(22);
-      r.best_id = (uint32_t)c1[23 * kBlock];
-      r.pad2 = f(24);
+      r.cur = (int)get(49);
+      r.sp = (int)get(50);
+      r.rid = get(51);
+      r.rec_idx = get(52);
+      r.pmeta = get(53);
+      r.code = (CodeT)((uint64_t)get(55) << 32 | get(54));
+      r.trail = (CodeT)((uint64_t)get(57) << 32 | get(56));
+      r.depth = (int)(get(58) & 0xFFu);
+      r.mirror = get(58) >> 8;
+      r.po = getf(59 + ln.c);
+      r.pi = getf(62 + ln.c);
+      r.dd = getf(65 + ln.c);
+      r.ptmin = getf(68);
+      r.pt0 = getf(69);
+      r.best_t = getf(70);
+      r.best_id = get(71);
+      r.pad2 = getf(72);
+      r.vpref = get(73);
       r.hu = s_uv[0][owner];
       r.hv = s_uv[1][owner];
 #pragma unroll
-      for (int a = 0; a < 4; ++a) r.g[a] = __int_as_float(c0[(16 * ln.c + 4 * a + ln.b) * kBlock]);
+      for (int a = 0; a < 4; ++a) r.g[a] = getf(16 * ln.c + 4 * a + ln.b);
       float4 ro, rd;
       group_open_ray(r, ln, s, bt, ro, rd);
       group_corner(r, leaf_scale);
@@ -693,12 +710,15 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
 // a wave, all of them in flight at once.  Bound by the heaviest ray's chain of
 // steps: 0.27 us per split and 0.67 us per recompute (375 instructions at one per 6
 // cycles, all that one wave issues) against 0.87 us for either on one lane.
-// 1024 rays of the torus: 270 -> 87 us; 16384 secondary rays: 621 -> 275 us.
-template <typename CodeT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_trace_wide(DeviceScene s,
+// 1024 rays of the torus: 270 -> 87 us; 16384 secondary rays: 621 -> 275 us, in the
+// learned order 797 -> 381 us (four waves per SIMD there: five spill 16 registers).
+template <bool kLearned, typename CodeT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kLearned ? 4 : 5))) void k_trace_wide(DeviceScene s,
                                                                                               BatchTable bt,
                                                                                               uint32_t groups) {
   __shared__ int stack[kMaxBvhDepth * kGroupsPerWave];
+  // learned order: 16 words per slot of the network's first column tile, of which the groups use four
+  __shared__ __align__(16) uint32_t s_feat[kLearned ? 16 * 16 : 4];
   const int lane = threadIdx.x;
   const uint32_t n = bt.prefix[bt.n_batches];
   const int L2 = 2 * s.leaf_depth;
@@ -710,7 +730,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
   r.mode = group < groups && r.rid < n ? kGroupFree : kGroupDead;
   bool first = true;
   int* column = stack + group;
-  group_loop<kGroupsPerWave>(r, ln, bt, L2, leaf_scale, lane, column, [&](uint64_t) {
+  group_loop<kGroupsPerWave, kLearned>(r, ln, bt, s.policy, s_feat, L2, leaf_scale, lane, column, [&](uint64_t) {
     const bool open = first;
     first = false;
     if (r.mode != kGroupFree) return;
@@ -725,6 +745,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
     r.hu = r.hv = 0.0f;
     r.cur = 0;
     r.sp = 0;
+    r.vpref = 0;
     if (ray_traced(ro, rd) && s.n_nodes > 0) {
       r.mode = kGroupWalk;
     } else {
@@ -878,11 +899,11 @@ int max_waves_per_cu(bool counted, bool learned, bool single_box, bool deep) {
   return counted ? resident_waves_per_cu<true, false, false, false>() : resident_waves_per_cu<false, false, false, false>();
 }
 
-template <typename CodeT>
+template <bool kLearned, typename CodeT>
 static int wide_waves_per_cu() {
   static const int per_cu = [] {
     int v = 0;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k_trace_wide<CodeT>, kBlock, 0);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k_trace_wide<kLearned, CodeT>, kBlock, 0);
     return std::max(1, v);
   }();
   return per_cu;
@@ -914,17 +935,21 @@ hipError_t launch_intersect(const DeviceScene& s, const BatchTable& bt, uint32_t
   if (waves_per_cu > 0) per_cu = std::min(per_cu, (int)waves_per_cu);
   const uint32_t waves = (uint32_t)(per_cu * s.n_cus);
   const dim3 block(kBlock);
-  if (!counters && !learned && !s.single_box && n <= kWideRaysPerCu * s.n_cus) {
-    int wide = deep ? wide_waves_per_cu<uint64_t>() : wide_waves_per_cu<uint32_t>();
+  if (!counters && !s.single_box && n <= kWideRaysPerCu * s.n_cus) {
+    int wide = deep      ? wide_waves_per_cu<false, uint64_t>()
+               : learned ? wide_waves_per_cu<true, uint32_t>()
+                         : wide_waves_per_cu<false, uint32_t>();
     if (waves_per_cu > 0) wide = std::min(wide, (int)waves_per_cu);
     const uint32_t room = (uint32_t)wide * s.n_cus;
     if (n <= kGroupsPerWave * room) {  // always, but under a small waves_per_cu
       const uint32_t groups = n <= room ? 1u : n <= 2u * room ? 2u : 4u;
       const dim3 grid((n + groups - 1) / groups);
       if (deep)
-        hipLaunchKernelGGL(k_trace_wide<uint64_t>, grid, block, 0, stream, s, bt, groups);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_trace_wide<false, uint64_t>), grid, block, 0, stream, s, bt, groups);
+      else if (learned)
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_trace_wide<true, uint32_t>), grid, block, 0, stream, s, bt, groups);
       else
-        hipLaunchKernelGGL(k_trace_wide<uint32_t>, grid, block, 0, stream, s, bt, groups);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_trace_wide<false, uint32_t>), grid, block, 0, stream, s, bt, groups);
       return hipGetLastError();
     }
   }

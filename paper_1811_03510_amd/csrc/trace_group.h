@@ -26,6 +26,7 @@
 
 #include "ccs_internal.h"
 #include "patch_math.h"
+#include "policy.h"
 #include "ray_valid.h"
 
 namespace ccs {
@@ -71,7 +72,10 @@ __device__ __forceinline__ void quad_transpose(float h[4], bool b0, bool b1) {
 }
 
 // What a group does next (a group that waits for a ray is kGroupFree).
-enum GroupMode : int { kGroupFree = 0, kGroupWalk = 1, kGroupStep = 2, kGroupGrid = 3, kGroupDead = 4 };
+enum GroupMode : int {
+  kGroupFree = 0, kGroupWalk = 1, kGroupStep = 2, kGroupGrid = 3, kGroupDead = 4,
+  kGroupDecide = 5  // learned order: waits for the network
+};
 
 template <typename CodeT>
 struct GroupRay {
@@ -96,6 +100,7 @@ struct GroupRay {
   float p[4];    // the record's points (i, j = b) of component c
   float pv[2];   // P^v of the inner points (1, j) and (2, j) of component c, j = 2 for b = 2, else 1
   float g[4];    // the working grid's row
+  uint32_t vpref;  // learned order: the v-half to take at the next split, as in the one-lane kernel
 };
 
 struct GroupLane {
@@ -279,9 +284,13 @@ __device__ __forceinline__ void group_grid(GroupRay<CodeT>& r, const GroupLane& 
 }
 
 // One subdivision step.  Returns false when the patch is finished (the caller
-// takes the next candidate from the stack or ends the ray).
-template <typename CodeT>
-__device__ __forceinline__ bool group_step(GroupRay<CodeT>& r, const GroupLane& ln, int L2, float leaf_scale) {
+// takes the next candidate from the stack or ends the ray).  Learned order: a split
+// along u where both halves are hit leaves the node's corners and slab results in
+// the group's 16 words at `feat` and its mirror bits in `mirror0`, and waits for
+// the network.
+template <bool kLearned, typename CodeT>
+__device__ __forceinline__ bool group_step(GroupRay<CodeT>& r, const GroupLane& ln, int L2, float leaf_scale,
+                                           uint32_t* feat, uint32_t& mirror0) {
   const Row7 e = casteljau_half(r.g[0], r.g[1], r.g[2], r.g[3]);
   const float la = quad_min(fminf(fminf(fminf(e.v[0], e.v[1]), e.v[2]), e.v[3]));
   const float ha = quad_max(fmaxf(fmaxf(fmaxf(e.v[0], e.v[1]), e.v[2]), e.v[3]));
@@ -297,11 +306,28 @@ __device__ __forceinline__ bool group_step(GroupRay<CodeT>& r, const GroupLane& 
   const bool mir = ((r.mirror >> axis) & 1u) != 0;
   const bool h_lo = mir ? hit_b : hit_a, h_up = mir ? hit_a : hit_b;
   const float t_lo = mir ? tb : ta, t_up = mir ? ta : tb;
-  const bool go_up = h_up && (!h_lo || t_up < t_lo);
+  bool go_up = h_up && (!h_lo || t_up < t_lo);
   const CodeT bit = (CodeT)1 << (L2 - 1 - r.depth);
+  bool decide = false;
+  if (kLearned) {
+    if ((r.vpref & 1u) && axis == 1 && hit_a && hit_b && r.depth != L2 - 1) go_up = (r.vpref & 2u) != 0;
+    r.vpref = 0;
+    decide = axis == 0 && hit_a && hit_b;
+  }
   const bool second = go_up != mir;
   if (hit_a || hit_b) {
     if (r.depth != L2 - 1) {
+      if (kLearned && decide) {
+        // the layout of policy_store_node: component c's corners (0,0), (3,0), (0,3), (3,3)
+        // at 4c, then the slab results
+        if (ln.b0 == ln.b1) {
+          float* o = reinterpret_cast<float*>(feat) + 4 * ln.c + (ln.b0 ? 2 : 0);
+          o[0] = e.v[0];
+          o[1] = e.v[6];
+        }
+        reinterpret_cast<float4*>(feat)[3] = make_float4(ta, xa, tb, xb);
+        mirror0 = r.mirror;
+      }
       r.g[0] = second ? e.v[6] : e.v[0];
       r.g[1] = second ? e.v[5] : e.v[1];
       r.g[2] = second ? e.v[4] : e.v[2];
@@ -317,6 +343,7 @@ __device__ __forceinline__ bool group_step(GroupRay<CodeT>& r, const GroupLane& 
       if (second) r.mirror ^= 1u << axis;
       r.depth++;
       if (r.pmeta & kGregoryBit) r.mode = kGroupGrid;
+      if (kLearned && decide) r.mode = kGroupDecide;
       return true;
     }
     const float tf = r.pt0 + (go_up ? t_up : t_lo);
@@ -338,6 +365,44 @@ __device__ __forceinline__ bool group_step(GroupRay<CodeT>& r, const GroupLane& 
   group_corner(r, leaf_scale);
   r.mode = kGroupGrid;
   return true;
+}
+
+// Learned order: the network for the groups that wait for it, by the whole wave.
+// feats: 16 words per group.
+template <typename CodeT>
+__device__ __forceinline__ void group_decide(GroupRay<CodeT>& r, const PolicyDev& policy, uint32_t* feats,
+                                             uint32_t mirror0, int L2, int lane, float leaf_scale) {
+  const uint64_t waiting = __ballot(r.mode == kGroupDecide);
+  if (waiting == 0) return;
+  const int group = lane / kGroupLanes, base = lane & ~(kGroupLanes - 1);
+  // the components' values from the group's three quads
+  const float fd = r.frames ? __builtin_amdgcn_rcpf(r.pi) : 0.0f;
+  const float px = __shfl(r.po, base), py = __shfl(r.po, base + 4), pz = __shfl(r.po, base + 8);
+  const float fx = __shfl(fd, base), fy = __shfl(fd, base + 4), fz = __shfl(fd, base + 8);
+  if (r.mode == kGroupDecide) {
+    float f[16];
+    policy_features(policy_load_node(feats, group, mirror0), px, py, pz, r.frames ? fx : r.dx, r.frames ? fy : r.dy,
+                    r.frames ? fz : r.dz, r.depth - 1, L2 / 2, (r.pmeta & kGregoryBit) != 0, f);
+    policy_store_inputs<16>(feats, group, f);
+  }
+  // a network input row per waiting group (16 columns of a tile, of which four are read)
+  uint64_t need = 0;
+#pragma unroll
+  for (int g = 0; g < kGroupsPerWave; ++g) need |= ((waiting >> (kGroupLanes * g)) & 1ull) << g;
+  policy_wave<16>(policy, feats, need, lane);
+  if (r.mode == kGroupDecide) {
+    const float4 lg = reinterpret_cast<const float4*>(feats)[4 * group];
+    const uint32_t top = policy_top(lg.x, lg.y, lg.z, lg.w);
+    const CodeT bit = (CodeT)1 << (L2 - r.depth);  // path bit of the u-split just taken
+    r.vpref = 1u | ((top & 1u) << 1);
+    if (((top >> 1) != 0) != ((r.code & bit) != 0)) {
+      r.code ^= bit;  // the other u-half first; the trail bit keeps the closest-first one pending
+      group_corner(r, leaf_scale);
+      r.mode = kGroupGrid;
+    } else {
+      r.mode = (r.pmeta & kGregoryBit) ? kGroupGrid : kGroupStep;
+    }
+  }
 }
 
 }  // namespace ccs

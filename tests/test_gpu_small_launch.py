@@ -44,9 +44,13 @@ def equal(ccs, scene, rays, n, parts=1):
     assert n < 500 or (ccs.hit_ids(got) != ccs.NO_HIT).any()
 
 
-@pytest.mark.parametrize("local,depth", [(True, 12), (False, 12), (True, 1), (True, 18), (False, 17)])
-def test_small_launches_match_one_lane_per_ray(ccs, c1, rays, local, depth):
+@pytest.mark.parametrize("local,depth,learned", [(True, 12, False), (False, 12, False), (True, 1, False),
+                                                 (True, 18, False), (False, 17, False), (True, 12, True),
+                                                 (False, 9, True)])
+def test_small_launches_match_one_lane_per_ray(ccs, c1, rays, local, depth, learned):
     scene = ccs.Scene(torch.from_numpy(c1.cp).cuda(), torch.from_numpy(c1.types).cuda(), depth, local_frames=local)
+    if learned:
+        scene.set_policy(torch.from_numpy(S.mlp_init()).cuda())
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     sizes = [1, 2, 3, 4, 5, 63, 65, 1000, 16 * cus, 20 * cus + 1, 40 * cus + 1, 64 * cus, 64 * cus + 1, 8 * 16 * cus + 1,
              8 * 64 * cus + 1, 12 * 64 * cus, 12 * 64 * cus + 1, 270000]
