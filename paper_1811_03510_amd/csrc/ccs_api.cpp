@@ -292,6 +292,16 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
   if (n > 0 && bvh.max_depth >= (uint32_t)kTraversalStack)
     return fail(CCS_ERR_UNSUPPORTED, "BVH deeper than the traversal stack");
 
+  // the refit's plan, of a large scene beside the records (26 ms for 1M patches)
+  ccs::RefitPlan plan;
+  auto make_plan = [&]() {
+    plan = ccs::plan_refit(bvh.nodes, bvh.leaf_parent, bvh.node_parent, ccs::kRefitCap0, ccs::kRefitCap1);
+  };
+  std::thread planner;
+  if (n >= (1u << 15))
+    planner = std::thread(make_plan);
+  else
+    make_plan();
   // records in leaf order
   std::vector<float> recs((size_t)n * ccs::kRecFloats, 0.0f);
   std::vector<uint32_t> inv_perm(n);
@@ -322,6 +332,7 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
     uint32_t meta = k | (types[k] == CCS_GREGORY ? ccs::kGregoryBit : 0u);
     std::memcpy(q + 63, &meta, 4);
   }
+  if (planner.joinable()) planner.join();
   s->build_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   s->device = dev;
   s->bvh_depth = bvh.max_depth;
@@ -334,7 +345,6 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
   float4* nodes = nullptr;
   uint32_t *perm = nullptr, *invp = nullptr, *blk_i = nullptr, *blk_n = nullptr, *nid = nullptr;
   int32_t *lpar = nullptr, *npar = nullptr, *iup = nullptr, *islot = nullptr, *nup = nullptr;
-  const ccs::RefitPlan plan = ccs::plan_refit(bvh.nodes, bvh.leaf_parent, bvh.node_parent, ccs::kRefitCap0, ccs::kRefitCap1);
   s->refit_passes = plan.passes;
   float* drec = nullptr;
   if ((st = dev_alloc(s, &nodes, (size_t)n_nodes * 4)) != CCS_OK || (st = dev_alloc(s, &drec, recs.size())) != CCS_OK ||

@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kRefitBlock) void k_refit_patches(DeviceScene s, co
 
 __global__ __launch_bounds__(kRefitCap1) void k_refit_boxes(float4* __restrict__ nodes,
                                                             const int32_t* __restrict__ node_parent, RefitDev plan,
-                                                            uint32_t first_block) {
+                                                            uint32_t first_block, uint32_t n_records) {
   __shared__ __align__(16) Treelets<kRefitCap1> tree;
   const uint32_t block = first_block + blockIdx.x;
   const uint32_t first = plan.block_items[block], end = plan.block_items[block + 1];
@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kRefitCap1) void k_refit_boxes(float4* __restrict__
   __syncthreads();
   const uint32_t k = first + threadIdx.x;
   if (k >= end) return;
-  const int32_t slot = plan.item_slot[k];
+  const int32_t slot = plan.item_slot[k - n_records];
   const float* f = reinterpret_cast<const float*>(nodes + 4 * (size_t)(slot >> 1)) + ((slot & 1) ? 6 : 0);
   float lo[3] = {f[0], f[1], f[2]}, hi[3] = {f[3], f[4], f[5]};
   tree.climb(nodes, node_parent, plan.item_up[k], lo, hi);
@@ -267,7 +267,7 @@ hipError_t launch_refit(const DeviceScene& s, const float* cp_world, const std::
       hipLaunchKernelGGL(k_refit_patches, grid, dim3(kRefitBlock), 0, stream, s, cp_world);
     else
       hipLaunchKernelGGL(k_refit_boxes, grid, dim3(kRefitCap1), 0, stream, const_cast<float4*>(s.nodes),
-                         s.node_parent, s.refit, passes[k].first_block);
+                         s.node_parent, s.refit, passes[k].first_block, s.n_patches);
   }
   return hipGetLastError();
 }

@@ -10,33 +10,32 @@ RefitPlan plan_refit(const std::vector<float>& nodes, const std::vector<int32_t>
   RefitPlan plan;
   const uint32_t n_nodes = (uint32_t)node_parent.size(), n = (uint32_t)leaf_parent.size();
   if (n == 0) return plan;
-  auto child = [&](uint32_t node, int side) {
+  auto child = [&](int32_t slot) {
     int32_t c;
-    std::memcpy(&c, nodes.data() + 16 * (size_t)node + 12 + side, 4);
+    std::memcpy(&c, nodes.data() + 16 * (size_t)(slot >> 1) + 12 + (slot & 1), 4);
     return c;
   };
-  // item[slot]: the slot's box is an item of the current pass; count[node]: items below it
-  std::vector<uint8_t> item(2 * (size_t)n_nodes, 0);
-  std::vector<uint32_t> count(n_nodes, 0);
-  std::vector<int32_t> local(n_nodes, -1);  // a node's index in its block
-  for (uint32_t r = 0; r < n; ++r) item[(size_t)leaf_parent[r]] = 1;
-  if (n == 1) item[1] = 0;  // a lone record fills both slots of the root: one item
-  std::vector<std::pair<int32_t, int32_t>> stack;  // (slot, its parent's index in the block or -1)
-  std::vector<uint32_t> live(n_nodes);  // nodes no treelet holds yet, parents first
-  for (uint32_t k = 0; k < n_nodes; ++k) live[k] = k;
+  std::vector<uint32_t> count(n_nodes, 0);   // items of the current pass below a node
+  std::vector<uint8_t> item(2 * (size_t)n_nodes, 0);  // from pass 1 on: the slot's box is an item
+  std::vector<int32_t> local(n_nodes);       // a node's index in its block
+  for (uint32_t r = 0; r < n; ++r) count[(uint32_t)leaf_parent[r] >> 1]++;
+  for (uint32_t k = n_nodes; k-- > 1;) count[(uint32_t)node_parent[k] >> 1] += count[k];  // children follow parents
+  plan.item_up.reserve(n + n / 16);
+  plan.node_id.reserve(n_nodes);
+  plan.node_up.reserve(n_nodes);
+  std::vector<uint32_t> live;                // nodes no treelet holds yet, parents first
+  std::vector<int32_t> next, above, stack;   // slots
   for (bool done = false; !done;) {
     const bool records = plan.passes.empty();
     const uint32_t cap = records ? cap0 : cap1;
     for (size_t q = live.size(); q-- > 0;) {
       const uint32_t k = live[q];
-      uint32_t c = 0;
-      for (int side = 0; side < 2; ++side) {
-        const size_t slot = 2 * (size_t)k + (size_t)side;
-        const int32_t ch = child(k, side);
-        c += item[slot] ? 1u : ch >= 0 ? count[(size_t)ch] : 0u;
-      }
-      count[k] = c;
+      count[k] = 0;
+      for (int32_t slot = (int32_t)(2 * k); slot < (int32_t)(2 * k + 2); ++slot)
+        count[k] += item[(size_t)slot] ? 1u : count[(size_t)child(slot)];
     }
+    live.clear();
+    next.clear();
     RefitPass pass;
     pass.first_block = (uint32_t)plan.block_items.size();
     uint32_t in_block = cap;  // full: the first item opens a block
@@ -49,50 +48,52 @@ RefitPlan plan_refit(const std::vector<float>& nodes, const std::vector<int32_t>
       }
       in_block += items;
     };
-    auto add_item = [&](int32_t slot, int32_t up) {
-      plan.item_up.push_back(up);
-      plan.item_slot.push_back(slot);
+    auto add_node = [&](uint32_t k, int32_t up) {
+      local[k] = (int32_t)((uint32_t)plan.node_id.size() - plan.block_nodes.back());
+      plan.node_id.push_back(k);
+      plan.node_up.push_back(up);
     };
-    std::vector<int32_t> next;    // slots that are items of the next pass
-    live.clear();
-    // walk from the root, left before right; -1 stands for the root itself
-    std::vector<int32_t> above = {-1};
+    auto link = [&](int32_t slot) { return local[(size_t)(slot >> 1)] << 1 | (slot & 1); };  // within the block
+    above.assign(1, -1);  // walked from the root (-1), left before right
     while (!above.empty()) {
       const int32_t slot = above.back();
       above.pop_back();
-      if (slot >= 0 && item[(size_t)slot]) {  // an item above every treelet
+      const int32_t ref = slot < 0 ? 0 : child(slot);
+      if (slot >= 0 && (records ? ref < 0 : item[(size_t)slot] != 0)) {  // an item above every treelet
         if (records) {  // its box still has to reach its slot
           room(1);
-          add_item(slot, -1);
+          plan.item_up.push_back(-1);
         }
         next.push_back(slot);
         continue;
       }
-      const uint32_t node = slot < 0 ? 0u : (uint32_t)child((uint32_t)slot >> 1, slot & 1);
-      if (count[node] > cap) {
+      const uint32_t node = (uint32_t)ref, size = count[node];
+      if (size > cap) {
         live.push_back(node);
         above.push_back((int32_t)(node << 1 | 1u));
         above.push_back((int32_t)(node << 1));
         continue;
       }
-      room(count[node]);
-      const uint32_t base = plan.block_nodes.back();
-      auto add_node = [&](uint32_t k, int32_t up) {
-        local[k] = (int32_t)((uint32_t)plan.node_id.size() - base);
-        plan.node_id.push_back(k);
-        plan.node_up.push_back(up);
-        stack.emplace_back((int32_t)(k << 1 | 1u), local[k]);
-        stack.emplace_back((int32_t)(k << 1), local[k]);
-      };
+      room(size);
       add_node(node, -1);
-      while (!stack.empty()) {
-        const auto [s, parent] = stack.back();
-        stack.pop_back();
-        const int32_t link = parent << 1 | (s & 1);
-        if (item[(size_t)s])
-          add_item(s, link);
-        else if (child((uint32_t)s >> 1, s & 1) >= 0)
-          add_node((uint32_t)child((uint32_t)s >> 1, s & 1), link);
+      if (records) {  // depth first: the subtree's nodes and records are two runs
+        for (uint32_t k = node + 1; k + 1 < node + size; ++k) add_node(k, link(node_parent[k]));
+        for (uint32_t q = 0; q < size; ++q) plan.item_up.push_back(link(leaf_parent[plan.item_up.size()]));
+      } else {
+        stack.assign({(int32_t)(node << 1 | 1u), (int32_t)(node << 1)});
+        while (!stack.empty()) {
+          const int32_t s = stack.back();
+          stack.pop_back();
+          if (item[(size_t)s]) {
+            plan.item_up.push_back(link(s));
+            plan.item_slot.push_back(s);
+            continue;
+          }
+          const uint32_t k = (uint32_t)child(s);
+          add_node(k, link(s));
+          stack.push_back((int32_t)(k << 1 | 1u));
+          stack.push_back((int32_t)(k << 1));
+        }
       }
       if (slot < 0)
         done = true;

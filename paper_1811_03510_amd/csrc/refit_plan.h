@@ -25,18 +25,17 @@ struct RefitPass {
 struct RefitPlan {
   std::vector<RefitPass> passes;
   // per block, and one end value after each pass's last block
-  std::vector<uint32_t> block_items;  // first item: a record (pass 0) or an index into item_slot / item_up
+  std::vector<uint32_t> block_items;  // first item: item k < n of pass 0 is record k
   std::vector<uint32_t> block_nodes;  // first entry of node_id / node_up
   std::vector<int32_t> item_up;       // item -> link to its parent among the block's nodes, -1: outside the block
-  std::vector<int32_t> item_slot;     // item -> the slot that holds its box (records: their slot)
+  std::vector<int32_t> item_slot;     // item k >= n -> the slot that holds its box, at k - n
   std::vector<uint32_t> node_id;      // node of a block -> node of the BVH
   std::vector<int32_t> node_up;       // node of a block -> link to its parent in the block, -1: a treelet's root
 };
 
 // nodes: 16 floats per node, the children's references as bits at 12 and 13 (>= 0
 // node, < 0 record ~child), in depth-first order (left child = node + 1); leaf_parent
-// and node_parent as the builder gives them.  Items of pass 0 come in record order,
-// so item k < leaf_parent.size() is record k.
+// and node_parent as the builder gives them.
 RefitPlan plan_refit(const std::vector<float>& nodes, const std::vector<int32_t>& leaf_parent,
                      const std::vector<int32_t>& node_parent, uint32_t cap0, uint32_t cap1);
 
