@@ -52,9 +52,8 @@ ccs_status device_cap(uint64_t& cap) {
   return CCS_OK;
 }
 
-// Every device allocation of the library goes through this pair.
-ccs_status raw_alloc(void** q, size_t bytes) {
-  *q = nullptr;
+// Counts `bytes` as held, unless that would exceed the cap.
+ccs_status reserve(size_t bytes) {
   uint64_t cap;
   ccs_status st = device_cap(cap);
   if (st != CCS_OK) return st;
@@ -65,6 +64,14 @@ ccs_status raw_alloc(void** q, size_t bytes) {
                                  "CCS_MAX_DEVICE_BYTES=" + std::to_string(cap) + " (" + std::to_string(before) +
                                  " bytes held)");
   }
+  return CCS_OK;
+}
+
+// Every device allocation of the library goes through this pair.
+ccs_status raw_alloc(void** q, size_t bytes) {
+  *q = nullptr;
+  const ccs_status st = reserve(bytes);
+  if (st != CCS_OK) return st;
   if (hipMalloc(q, bytes) != hipSuccess) {
     (void)hipGetLastError();
     g_live_bytes.fetch_sub(bytes);
@@ -715,15 +722,14 @@ ccs_status ccs_policy_infer(const float* params, const float* features, uint32_t
   g_error.clear();
   if (n == 0) return CCS_OK;
   if (!params || !features || !logits) return fail(CCS_ERR_INVALID_ARG, "a pointer is NULL");
-  Scratch sc;
-  uint2* w = nullptr;
-  float4* b = nullptr;
-  ccs_status st = sc.alloc(&w, (size_t)ccs::kPolicyWTiles * 64);
-  if (st == CCS_OK) st = sc.alloc(&b, (size_t)ccs::kPolicyBTiles * 64);
+  // The inference holds no device memory of its own.  Its packed operands used to be a
+  // temporary, and a cap that refused them still refuses the call.
+  constexpr size_t kOperands = 64 * (ccs::kPolicyWTiles * sizeof(uint2) + ccs::kPolicyBTiles * sizeof(float4));
+  ccs_status st = reserve(kOperands);
   if (st != CCS_OK) return st;
+  g_live_bytes.fetch_sub(kOperands);
   hipStream_t str = (hipStream_t)stream;
-  hipError_t e = ccs::launch_policy_pack(params, w, b, str);
-  if (e == hipSuccess) e = ccs::launch_policy_infer(ccs::PolicyDev{w, b}, features, n, logits, str);
+  hipError_t e = ccs::launch_policy_infer(params, features, n, logits, str);
   if (e == hipSuccess) e = hipStreamSynchronize(str);
   if (e != hipSuccess) return hip_fail(e, "policy inference");
   return CCS_OK;

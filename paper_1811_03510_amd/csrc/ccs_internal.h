@@ -92,7 +92,7 @@ hipError_t launch_intersect(const DeviceScene& s, const BatchTable& bt, uint32_t
 hipError_t launch_refit(const DeviceScene& s, const float* cp_world, const std::vector<RefitPass>& passes,
                         hipStream_t stream);
 hipError_t launch_policy_pack(const float* params, uint2* w, float4* b, hipStream_t stream);
-hipError_t launch_policy_infer(const PolicyDev& P, const float* x, uint32_t n, float* z, hipStream_t stream);
+hipError_t launch_policy_infer(const float* params, const float* x, uint32_t n, float* z, hipStream_t stream);
 hipError_t launch_record(const DeviceScene& s, const ccs_ray* rays, const ccs_hit* hits, uint32_t n, float* feats,
                          uint8_t* labels, hipStream_t stream);
 hipError_t launch_mlp_grad(const float* theta, const float* X, const uint8_t* Y, uint32_t n, uint32_t batch,

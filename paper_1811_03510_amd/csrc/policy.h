@@ -160,14 +160,16 @@ __device__ __forceinline__ PolicyRaw policy_load_node(const uint32_t* slots, int
 // transposed (H^T = W X^T) so that each layer's accumulator layout is the next
 // layer's B operand: lane l holds, for sample (l & 15) of the tile, inputs
 // 4 (l >> 4) .. +3 in `x`, and receives in the returned vector, when l < 16,
-// the tile's logits 0..3 of sample l.  Must be executed by the whole wave.
-__device__ __forceinline__ f32x4 policy_tile(const PolicyDev& P, bf16x4 x, int lane) {
+// the tile's logits 0..3 of sample l.  w(t) and b(t) give the lane's operands of weight
+// tile t and bias tile t.  Must be executed by the whole wave.
+template <typename Weight, typename Bias>
+__device__ __forceinline__ f32x4 policy_tile(Weight w, Bias b, bf16x4 x) {
   const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
   bf16x4 h1[2], h2[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(P.w[t * 64 + lane]), x, zero, 0, 0, 0);
-    const float4 bb = P.b[t * 64 + lane];
+    f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(w(t)), x, zero, 0, 0, 0);
+    const float4 bb = b(t);
     uint2 hv;
     hv.x = bf16_pair(fmaxf(acc[0] + bb.x, 0.0f), fmaxf(acc[1] + bb.y, 0.0f));
     hv.y = bf16_pair(fmaxf(acc[2] + bb.z, 0.0f), fmaxf(acc[3] + bb.w, 0.0f));
@@ -175,17 +177,17 @@ __device__ __forceinline__ f32x4 policy_tile(const PolicyDev& P, bf16x4 x, int l
   }
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
-    f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(P.w[(2 + 2 * t) * 64 + lane]), h1[0], zero, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(P.w[(3 + 2 * t) * 64 + lane]), h1[1], acc, 0, 0, 0);
-    const float4 bb = P.b[(2 + t) * 64 + lane];
+    f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(w(2 + 2 * t)), h1[0], zero, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(w(3 + 2 * t)), h1[1], acc, 0, 0, 0);
+    const float4 bb = b(2 + t);
     uint2 hv;
     hv.x = bf16_pair(fmaxf(acc[0] + bb.x, 0.0f), fmaxf(acc[1] + bb.y, 0.0f));
     hv.y = bf16_pair(fmaxf(acc[2] + bb.z, 0.0f), fmaxf(acc[3] + bb.w, 0.0f));
     h2[t] = as_bf16x4(hv);
   }
-  f32x4 z = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(P.w[6 * 64 + lane]), h2[0], zero, 0, 0, 0);
-  z = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(P.w[7 * 64 + lane]), h2[1], z, 0, 0, 0);
-  const float4 bb = P.b[4 * 64 + lane];
+  f32x4 z = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(w(6)), h2[0], zero, 0, 0, 0);
+  z = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as_bf16x4(w(7)), h2[1], z, 0, 0, 0);
+  const float4 bb = b(4);
   z[0] += bb.x;
   z[1] += bb.y;
   z[2] += bb.z;
@@ -213,7 +215,8 @@ __device__ __forceinline__ void policy_wave(const PolicyDev& P, uint32_t* feat, 
   for (int c = 0; c < 4; ++c) {
     if (((need >> (16 * c)) & 0xFFFFull) == 0) continue;
     const uint2 xv = *reinterpret_cast<const uint2*>(feat + (16 * c + (lane & 15)) * kSlot + 2 * (lane >> 4));
-    const f32x4 z = policy_tile(P, as_bf16x4(xv), lane);
+    const f32x4 z = policy_tile([&](int t) { return P.w[t * 64 + lane]; }, [&](int t) { return P.b[t * 64 + lane]; },
+                                as_bf16x4(xv));
     if (lane < 16)
       *reinterpret_cast<float4*>(feat + (16 * c + lane) * kSlot) = make_float4(z[0], z[1], z[2], z[3]);
   }
