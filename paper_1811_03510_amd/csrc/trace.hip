@@ -19,8 +19,10 @@
 //
 // A launch's last rays are few and long (the heaviest of 460k takes 2600 steps and
 // recomputes, the mean is 40): once the queue is empty and a wave holds at most
-// kTailRays of them, it spreads each over 16 lanes (trace_group.h), and launches of
-// few rays run that way from the start (k_trace_wide).  Bits are the same.
+// kTailRays of them, it spreads each over 16 lanes and its last one over all 64
+// (trace_group.h); launches of few rays run a wave per ray from the start
+// (k_trace_solo; in the learned order 16 lanes, k_trace_wide_learned).  Bits are the
+// same.
 //
 // Alg. 3 state per lane (registers only, no stack):
 //   code  interleaved path bits of the current domain; split k (u at even k)
@@ -47,11 +49,13 @@ namespace ccs {
 
 constexpr int kBlock = 64;
 // Once the queue is empty a wave keeps one ray per lane until this many are left and
-// then gives each 16 lanes (trace_group.h).  Measured on a field of 200 objects in
-// world frames (460k rays), 16 animation frames of the torus and a two-bounce path
-// at 1280x720: 4, 8, 12, 16 and 21 give the same times within their spread (at 4
-// the torus' 32k rays take 6 % longer), 0 takes 1.3 to 1.5 times as long.
-constexpr int kTailRays = 12;
+// then gives each 16 lanes (trace_group.h), the last one all 64.  6, 8 and 12 give the
+// same times within their spread on a field of 200 objects in world frames (460k
+// rays), 16 animation frames of the torus, 1M patches and a two-bounce path at
+// 1280x720; at 1, 2 and 4 the torus' 32k rays take 452, 405 and 387 us against
+// 290, the path 2291, 2108 and 2035 against 1860 us.
+constexpr int kTailRays = 8;
+constexpr int kSoloWaves = 5;  // waves per SIMD of the wave-per-ray kernel
 constexpr uint32_t kGridOwners = kBlock / 3;  // lanes whose grids one recompute phase serves
 
 enum Mode : int { kFetch = 0, kTraverse = 1, kStep = 2, kGrid = 3, kDead = 4, kDecide = 5 };
@@ -111,12 +115,54 @@ __device__ __forceinline__ void write_hit(const BatchTable& bt, uint32_t* __rest
 // a hit leaf box is recorded at its own entry distance.  No distance orders the
 // halves, and every pending half costs a grid recompute.
 
+// A wave's single ray to its end; every value of r is the same in all groups.
+template <int kStride, typename CodeT>
+__device__ __forceinline__ void solo_loop(GroupRay<CodeT>& r, const GroupLane& ln, const BatchTable& bt, int L2,
+                                          float leaf_scale, int lane, int* stack) {
+  int cur = uniform(r.cur), sp = uniform(r.sp);  // sp < 0: the ray is done
+  for (float* x : {&r.ox, &r.oy, &r.oz, &r.dx, &r.dy, &r.dz, &r.tmin}) *x = uniform(*x);
+  r.nodes = uniform(r.nodes);
+  r.recs = uniform(r.recs);
+  r.frames = uniform(r.frames);
+  r.rid = uniform(r.rid);
+  bool walk = uniform(r.mode) == kGroupWalk;
+  while (sp >= 0) {
+    bool found = !walk;
+    while (walk) {
+      if (cur < 0) {
+        r.cur = cur;
+        group_candidate(r, ln);
+        found = true;
+        break;
+      }
+      float t0, t1;
+      const int2 ch = group_children(r, ln, cur, t0, t1);
+      const int seen = uniform((t0 != __builtin_inff() ? 1 : 0) | (t1 != __builtin_inff() ? 2 : 0) | (t1 < t0 ? 4 : 0));
+      const int c0 = uniform(ch.x), c1 = uniform(ch.y);
+      if ((seen & 3) == 0) break;
+      const bool first1 = (seen & 4) != 0;  // also where only the second child is met (a missed box is at +inf)
+      if ((seen & 3) == 3 && sp < (int)kMaxBvhDepth) {  // always holds: the host rejects deeper BVHs
+        stack[sp * kStride] = first1 ? c0 : c1;
+        ++sp;
+      }
+      cur = first1 ? c1 : c0;
+    }
+    if (found) solo_patch(r, ln, L2, leaf_scale, lane);
+    if (--sp >= 0) cur = uniform(stack[sp * kStride]);
+    walk = true;
+  }
+  if (lane == 0) {
+    const Counts zero = {0, 0, 0, 0, 0, 0, 0, 0};
+    write_hit<false>(bt, nullptr, r.rid, r.best_t, r.best_id, r.hu, r.hv, zero);
+  }
+}
+
 // Runs a wave's groups until every one is dead.  next(want) gives the groups whose
 // lanes are set in `want` a ray each, or ends them.
 template <int kStride, bool kLearned, typename CodeT, typename Next>
 __device__ __forceinline__ void group_loop(GroupRay<CodeT>& r, const GroupLane& ln, const BatchTable& bt,
                                            const PolicyDev& policy, uint32_t* feats, int L2, float leaf_scale, int lane,
-                                           int*& stack, Next next) {
+                                           int* base, int*& stack, Next next) {
   uint32_t mirror0 = 0;  // learned order: mirror bits of the node that waits for the network
   auto finish = [&]() {
     if ((lane & (kGroupLanes - 1)) == 0) {
@@ -128,7 +174,16 @@ __device__ __forceinline__ void group_loop(GroupRay<CodeT>& r, const GroupLane& 
   for (;;) {
     const uint64_t want = __ballot(r.mode == kGroupFree);
     if (want != 0) next(want);
-    if (__ballot(r.mode != kGroupDead) == 0) break;
+    const uint64_t live = __ballot(r.mode != kGroupDead);
+    if (live == 0) break;
+    if (!kLearned && __popcll(live) == kGroupLanes && __ballot(r.mode == kGroupFree) == 0) {
+      // the wave's last ray: all groups carry it
+      const int owner = __ffsll((unsigned long long)live) - 1;
+      spread(r, owner, lane);
+      const int at = __shfl((int)(stack - base), owner);
+      solo_loop<kStride>(r, ln, bt, L2, leaf_scale, lane, base + at);
+      break;
+    }
     if (r.mode == kGroupWalk) {
       for (int it = 0; it < kGroupNodeSteps && r.mode == kGroupWalk; ++it) {
         if (r.cur < 0)
@@ -137,7 +192,7 @@ __device__ __forceinline__ void group_loop(GroupRay<CodeT>& r, const GroupLane& 
           finish();
       }
     }
-    if (r.mode == kGroupGrid) group_grid(r, ln);
+    if (r.mode == kGroupGrid) group_grid<1>(r, ln);
     if (r.mode == kGroupStep) {
       if (!group_step<kLearned>(r, ln, L2, leaf_scale, feats + 16 * (lane / kGroupLanes), mirror0)) {
         if (r.sp > 0) {
@@ -654,7 +709,7 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
     int* column = stack;
     uint32_t taken = 0;
     const uint32_t n_live = (uint32_t)__popcll(busy);
-    group_loop<kBlock, kLearned>(r, ln, bt, s.policy, s_feat, L2, leaf_scale, lane, column, [&](uint64_t want) {
+    group_loop<kBlock, kLearned>(r, ln, bt, s.policy, s_feat, L2, leaf_scale, lane, stack, column, [&](uint64_t want) {
       const uint32_t k = taken + (uint32_t)__popcll(want & ((1ull << (lane & ~(kGroupLanes - 1))) - 1ull)) / kGroupLanes;
       taken += (uint32_t)__popcll(want) / kGroupLanes;
       if (r.mode != kGroupFree) return;
@@ -706,31 +761,52 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
   }
 }
 
-// Small launches: every ray on 16 lanes from the start, `groups` (1, 2 or 4) rays to
-// a wave, all of them in flight at once.  Bound by the heaviest ray's chain of
-// steps: 0.27 us per split and 0.67 us per recompute (375 instructions at one per 6
-// cycles, all that one wave issues) against 0.87 us for either on one lane.
-// 1024 rays of the torus: 270 -> 87 us; 16384 secondary rays: 621 -> 275 us, in the
-// learned order 797 -> 381 us (four waves per SIMD there: five spill 16 registers).
-template <bool kLearned, typename CodeT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kLearned ? 4 : 5))) void k_trace_wide(DeviceScene s,
-                                                                                              BatchTable bt,
-                                                                                              uint32_t groups) {
+// Small launches: a wave per ray (solo_loop).  Bound by the heaviest ray's chain of
+// steps, about 110 instructions per Bezier step and 500 per four expanded Gregory
+// nodes at one instruction per 6 cycles, all that one wave issues: the heaviest of
+// 16384 secondary rays of the torus (186 splits, 218 recomputes) takes 98 us alone,
+// against 175 us on 16 lanes and 354 us on one.
+// 1024 primary rays of the torus: 270 -> 76 us; 8192 / 16384 secondary ones: 635 / 621
+// -> 160 / 242 us.
+template <typename CodeT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSoloWaves))) void k_trace_solo(
+    DeviceScene s, BatchTable bt) {
+  __shared__ int stack[kMaxBvhDepth];
+  const int lane = threadIdx.x;
+  const GroupLane ln(lane);
+  GroupRay<CodeT> r;
+  r.rid = blockIdx.x;
+  float4 ro, rd;
+  group_open_ray(r, ln, s, bt, ro, rd);
+  r.best_t = rd.w;
+  r.best_id = kNoHit;
+  r.hu = r.hv = 0.0f;
+  r.cur = 0;
+  r.sp = ray_traced(ro, rd) && s.n_nodes > 0 ? 0 : -1;
+  r.mode = kGroupWalk;
+  solo_loop<1>(r, ln, bt, 2 * s.leaf_depth, __uint_as_float((uint32_t)(127 - s.leaf_depth) << 23), lane, stack);
+}
+
+// Small launches in the learned order: every ray on 16 lanes from the start, `groups`
+// (1, 2 or 4) rays to a wave, all of them in flight at once.  16384 torus rays:
+// 797 -> 381 us.
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_trace_wide_learned(
+    DeviceScene s, BatchTable bt, uint32_t groups) {
   __shared__ int stack[kMaxBvhDepth * kGroupsPerWave];
-  // learned order: 16 words per slot of the network's first column tile, of which the groups use four
-  __shared__ __align__(16) uint32_t s_feat[kLearned ? 16 * 16 : 4];
+  // 16 words per slot of the network's first column tile, of which the groups use four
+  __shared__ __align__(16) uint32_t s_feat[16 * 16];
   const int lane = threadIdx.x;
   const uint32_t n = bt.prefix[bt.n_batches];
   const int L2 = 2 * s.leaf_depth;
   const float leaf_scale = __uint_as_float((uint32_t)(127 - s.leaf_depth) << 23);
   const GroupLane ln(lane);
   const uint32_t group = (uint32_t)lane / kGroupLanes;
-  GroupRay<CodeT> r;
+  GroupRay<uint32_t> r;
   r.rid = blockIdx.x * groups + group;
   r.mode = group < groups && r.rid < n ? kGroupFree : kGroupDead;
   bool first = true;
   int* column = stack + group;
-  group_loop<kGroupsPerWave, kLearned>(r, ln, bt, s.policy, s_feat, L2, leaf_scale, lane, column, [&](uint64_t) {
+  group_loop<kGroupsPerWave, true>(r, ln, bt, s.policy, s_feat, L2, leaf_scale, lane, stack, column, [&](uint64_t) {
     const bool open = first;
     first = false;
     if (r.mode != kGroupFree) return;
@@ -899,22 +975,23 @@ int max_waves_per_cu(bool counted, bool learned, bool single_box, bool deep) {
   return counted ? resident_waves_per_cu<true, false, false, false>() : resident_waves_per_cu<false, false, false, false>();
 }
 
-template <bool kLearned, typename CodeT>
 static int wide_waves_per_cu() {
   static const int per_cu = [] {
     int v = 0;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k_trace_wide<kLearned, CodeT>, kBlock, 0);
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k_trace_wide_learned, kBlock, 0);
     return std::max(1, v);
   }();
   return per_cu;
 }
 
-// Launches of at most this many rays per compute unit (16384 on 256) take
-// k_trace_wide.  Per-ray work is about three times the one-lane kernel's, so it
-// loses once the machine is full: 16384 / 24000 / 32768 secondary rays of the torus
-// take 275 / 363 / 485 us against 374 / 363 / 366 us with one ray per lane, of 200
-// objects 331 / 484 / 570 against 503 / 548 / 552 us, and in world frames
-// 725 / 1311 / 1533 against 932 / 1512 / 1726 us.
+// Launches of at most this many rays per compute unit (24576 on 256) take a wave per
+// ray.  Per-ray work is several times the one-lane kernel's, so it loses once the
+// machine is full: 16384 / 24576 / 30000 / 50000 secondary rays of the torus take 242 /
+// 261 / 329 / 443 us against 288 / 289 / 289 / 312 with a ray per lane, of 200 objects
+// 262 / 367 / 412 / 622 against 428 / 458 / 457 / 497 us, and in world frames 574 /
+// 961 / 1037 / 1192 against 844 / 1067 / 1139 / 1164 us.
+constexpr uint32_t kSoloRaysPerCu = 96;
+// The learned order's 16-lane kernel: 16384 torus rays 381 us, 20000 on one lane each 680 us.
 constexpr uint32_t kWideRaysPerCu = 64;
 
 // Fewest lanes of a wave that take rays in a launch that all lanes could hold at
@@ -935,21 +1012,20 @@ hipError_t launch_intersect(const DeviceScene& s, const BatchTable& bt, uint32_t
   if (waves_per_cu > 0) per_cu = std::min(per_cu, (int)waves_per_cu);
   const uint32_t waves = (uint32_t)(per_cu * s.n_cus);
   const dim3 block(kBlock);
-  if (!counters && !s.single_box && n <= kWideRaysPerCu * s.n_cus) {
-    int wide = deep      ? wide_waves_per_cu<false, uint64_t>()
-               : learned ? wide_waves_per_cu<true, uint32_t>()
-                         : wide_waves_per_cu<false, uint32_t>();
-    if (waves_per_cu > 0) wide = std::min(wide, (int)waves_per_cu);
-    const uint32_t room = (uint32_t)wide * s.n_cus;
-    if (n <= kGroupsPerWave * room) {  // always, but under a small waves_per_cu
+  // small launches (a small waves_per_cu keeps those that would exceed it on one lane per ray)
+  const uint32_t limit = waves_per_cu > 0 ? waves_per_cu * s.n_cus : 0xFFFFFFFFu;
+  if (!counters && !s.single_box && !learned && n <= std::min(limit, kSoloRaysPerCu * s.n_cus)) {
+    if (deep)
+      hipLaunchKernelGGL(k_trace_solo<uint64_t>, dim3(n), block, 0, stream, s, bt);
+    else
+      hipLaunchKernelGGL(k_trace_solo<uint32_t>, dim3(n), block, 0, stream, s, bt);
+    return hipGetLastError();
+  }
+  if (!counters && learned && n <= kWideRaysPerCu * s.n_cus) {
+    const uint32_t room = std::min(limit, (uint32_t)wide_waves_per_cu() * s.n_cus);
+    if (n <= kGroupsPerWave * room) {
       const uint32_t groups = n <= room ? 1u : n <= 2u * room ? 2u : 4u;
-      const dim3 grid((n + groups - 1) / groups);
-      if (deep)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_trace_wide<false, uint64_t>), grid, block, 0, stream, s, bt, groups);
-      else if (learned)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_trace_wide<true, uint32_t>), grid, block, 0, stream, s, bt, groups);
-      else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k_trace_wide<false, uint32_t>), grid, block, 0, stream, s, bt, groups);
+      hipLaunchKernelGGL(k_trace_wide_learned, dim3((n + groups - 1) / groups), block, 0, stream, s, bt, groups);
       return hipGetLastError();
     }
   }

@@ -3,13 +3,14 @@
 // DPP row), four rays to a wave.
 //
 // Why: with one ray per lane a subdivision step is ~340 vector instructions and a
-// recompute ~430, issued at one per four cycles, so a single ray advances a
-// Gregory level every 1.9 us however empty the machine is, and a launch lasts at
-// least as long as its heaviest ray (up to ~1700 steps and recomputes on a grazing
-// ray, where the mean is 40).  Spread over 16 lanes the same step is ~110
-// instructions and the recompute ~190, without a memory access (the record stays
-// in registers).  Per ray it issues about three times as many instructions, so it
-// is used only where lanes would idle: small launches and the last rays of a wave.
+// recompute ~430, issued at one per six cycles (all that one wave issues), so a single
+// ray advances a Gregory level every 1.9 us however empty the machine is, and a launch
+// lasts at least as long as its heaviest ray (up to ~1700 steps and recomputes on a
+// grazing ray, where the mean is 40).  Spread over 16 lanes the same step is ~140
+// instructions and the recompute ~220, without a memory access (the record stays in
+// registers): 0.94 us per Gregory level.  With all 64 lanes on one ray, below, it is
+// 0.47 us.  Per ray this issues several times as many instructions, so it is used only
+// where lanes would idle: small launches and the last rays of a wave.
 //
 // Lane l of a group: b = l & 3, q = l >> 2, component c = min(q, 2) (q = 3 repeats
 // z, so that a reduction over the four quads is one over the three components).
@@ -194,11 +195,12 @@ __device__ __forceinline__ void group_candidate(GroupRay<CodeT>& r, const GroupL
   }
 }
 
-// One BVH node: lane (c, b) tests component c of child b & 1.  The node stack of
-// the ray is stack[kStride * level].  Returns false when the ray is done.
-template <int kStride, typename CodeT>
-__device__ __forceinline__ bool group_node(GroupRay<CodeT>& r, const GroupLane& ln, int* stack) {
-  const float* nd = reinterpret_cast<const float*>(r.nodes + 4 * (size_t)r.cur);
+// The children of a BVH node and the distances at which their boxes are entered (+inf:
+// missed); lane (c, b) tests component c of child b & 1.
+template <typename CodeT>
+__device__ __forceinline__ int2 group_children(const GroupRay<CodeT>& r, const GroupLane& ln, int node, float& t0,
+                                               float& t1) {
+  const float* nd = reinterpret_cast<const float*>(r.nodes + 4 * (size_t)node);
   const int at = (ln.b0 ? 6 : 0) + ln.c;
   const float lo = nd[at], hi = nd[at + 3];
   const int2 ch = *reinterpret_cast<const int2*>(nd + 12);
@@ -208,7 +210,17 @@ __device__ __forceinline__ bool group_node(GroupRay<CodeT>& r, const GroupLane& 
   const float fr = fminf(widen_far(across_min(fmaxf(x0, x1))), capw);
   const float own = nr <= fr ? nr : __builtin_inff();
   const float other = dpp<kQuadXor1>(own);
-  const float t0 = ln.b0 ? other : own, t1 = ln.b0 ? own : other;
+  t0 = ln.b0 ? other : own;
+  t1 = ln.b0 ? own : other;
+  return ch;
+}
+
+// One BVH node.  The node stack of the ray is stack[kStride * level].  Returns false
+// when the ray is done.
+template <int kStride, typename CodeT>
+__device__ __forceinline__ bool group_node(GroupRay<CodeT>& r, const GroupLane& ln, int* stack) {
+  float t0, t1;
+  const int2 ch = group_children(r, ln, r.cur, t0, t1);
   const bool h0 = t0 != __builtin_inff(), h1 = t1 != __builtin_inff();
   if (h0 && h1) {
     const bool first1 = t1 < t0;
@@ -231,13 +243,14 @@ __device__ __forceinline__ bool group_node(GroupRay<CodeT>& r, const GroupLane& 
 // The current domain's grid (and Gregory displacement): Alg. 2 and the crop of
 // calc_component, one column j = b of the points per lane for the u pass, one
 // row i = b for the v pass.
-template <typename CodeT>
+// kGregory: 0 a Bezier patch, 2 a Gregory patch, 1 as its meta word says.
+template <int kGregory, typename CodeT>
 __device__ __forceinline__ void group_grid(GroupRay<CodeT>& r, const GroupLane& ln) {
   const float su = __uint_as_float((uint32_t)(127 - ((r.depth + 1) >> 1)) << 23);
   const float sv = __uint_as_float((uint32_t)(127 - (r.depth >> 1)) << 23);
   const float u0 = r.u0, u1 = u0 + su, v0 = r.v0, v1 = v0 + sv;
   float p0 = r.p[0], p1 = r.p[1], p2 = r.p[2], p3 = r.p[3], d = 0.0f;
-  if (r.pmeta & kGregoryBit) {
+  if (kGregory == 2 || (kGregory == 1 && (r.pmeta & kGregoryBit))) {
     const bool inner = ln.b0 != ln.b1;  // j = 1 or 2
     const float wv1 = wbar1(v0, v1), wv2 = wbar2(v0, v1), wv = ln.j2 ? wv2 : wv1;
     const float dvl = ln.j2 ? 1.0f - v1 : v0, dvh = ln.j2 ? 1.0f - v0 : v1;
@@ -283,6 +296,47 @@ __device__ __forceinline__ void group_grid(GroupRay<CodeT>& r, const GroupLane& 
   r.mode = kGroupStep;
 }
 
+// Both halves of the working grid: the points of the lane's row, and entry, exit and
+// hit of the halves in storage order, against the best distance so far.
+struct GroupSplit {
+  Row7 e;
+  float ta, xa, tb, xb;
+  bool hit_a, hit_b;
+};
+
+template <typename CodeT>
+__device__ __forceinline__ GroupSplit group_split(const GroupRay<CodeT>& r) {
+  GroupSplit h;
+  h.e = casteljau_half(r.g[0], r.g[1], r.g[2], r.g[3]);
+  const Row7& e = h.e;
+  const float la = quad_min(fminf(fminf(fminf(e.v[0], e.v[1]), e.v[2]), e.v[3]));
+  const float ha = quad_max(fmaxf(fmaxf(fmaxf(e.v[0], e.v[1]), e.v[2]), e.v[3]));
+  const float lb = quad_min(fminf(fminf(fminf(e.v[3], e.v[4]), e.v[5]), e.v[6]));
+  const float hb = quad_max(fmaxf(fmaxf(fmaxf(e.v[3], e.v[4]), e.v[5]), e.v[6]));
+  const float a0 = (la - r.po) * r.pi, a1 = (ha + r.dd - r.po) * r.pi;
+  const float b0 = (lb - r.po) * r.pi, b1 = (hb + r.dd - r.po) * r.pi;
+  h.ta = fmaxf(across_max(fminf(a0, a1)), r.ptmin);
+  h.xa = across_min(fmaxf(a0, a1));
+  h.tb = fmaxf(across_max(fminf(b0, b1)), r.ptmin);
+  h.xb = across_min(fmaxf(b0, b1));
+  const float cap = (r.best_t - r.pt0) + (fabsf(r.best_t) + fabsf(r.pt0)) * 0x1p-22f;
+  h.hit_a = h.ta <= fminf(widen_far(h.xa), cap);
+  h.hit_b = h.tb <= fminf(widen_far(h.xb), cap);
+  return h;
+}
+
+// A leaf entered at distance tf with path code lc, recorded when it is the best.
+template <typename CodeT>
+__device__ __forceinline__ bool group_leaf(GroupRay<CodeT>& r, float tf, CodeT lc, float leaf_scale) {
+  const uint32_t pid = r.pmeta & kIdMask;
+  if (!(tf < r.best_t || (tf == r.best_t && pid < r.best_id))) return false;
+  r.best_t = tf;
+  r.best_id = pid;
+  r.hu = (float)(2u * compact_even(lc >> 1) + 1u) * (0.5f * leaf_scale);
+  r.hv = (float)(2u * compact_even(lc) + 1u) * (0.5f * leaf_scale);
+  return true;
+}
+
 // One subdivision step.  Returns false when the patch is finished (the caller
 // takes the next candidate from the stack or ends the ray).  Learned order: a split
 // along u where both halves are hit leaves the node's corners and slab results in
@@ -291,17 +345,10 @@ __device__ __forceinline__ void group_grid(GroupRay<CodeT>& r, const GroupLane& 
 template <bool kLearned, typename CodeT>
 __device__ __forceinline__ bool group_step(GroupRay<CodeT>& r, const GroupLane& ln, int L2, float leaf_scale,
                                            uint32_t* feat, uint32_t& mirror0) {
-  const Row7 e = casteljau_half(r.g[0], r.g[1], r.g[2], r.g[3]);
-  const float la = quad_min(fminf(fminf(fminf(e.v[0], e.v[1]), e.v[2]), e.v[3]));
-  const float ha = quad_max(fmaxf(fmaxf(fmaxf(e.v[0], e.v[1]), e.v[2]), e.v[3]));
-  const float lb = quad_min(fminf(fminf(fminf(e.v[3], e.v[4]), e.v[5]), e.v[6]));
-  const float hb = quad_max(fmaxf(fmaxf(fmaxf(e.v[3], e.v[4]), e.v[5]), e.v[6]));
-  const float a0 = (la - r.po) * r.pi, a1 = (ha + r.dd - r.po) * r.pi;
-  const float b0 = (lb - r.po) * r.pi, b1 = (hb + r.dd - r.po) * r.pi;
-  const float ta = fmaxf(across_max(fminf(a0, a1)), r.ptmin), xa = across_min(fmaxf(a0, a1));
-  const float tb = fmaxf(across_max(fminf(b0, b1)), r.ptmin), xb = across_min(fmaxf(b0, b1));
-  const float cap = (r.best_t - r.pt0) + (fabsf(r.best_t) + fabsf(r.pt0)) * 0x1p-22f;
-  const bool hit_a = ta <= fminf(widen_far(xa), cap), hit_b = tb <= fminf(widen_far(xb), cap);
+  const GroupSplit h = group_split(r);
+  const Row7& e = h.e;
+  const float ta = h.ta, xa = h.xa, tb = h.tb, xb = h.xb;
+  const bool hit_a = h.hit_a, hit_b = h.hit_b;
   const int axis = r.depth & 1;
   const bool mir = ((r.mirror >> axis) & 1u) != 0;
   const bool h_lo = mir ? hit_b : hit_a, h_up = mir ? hit_a : hit_b;
@@ -346,15 +393,7 @@ __device__ __forceinline__ bool group_step(GroupRay<CodeT>& r, const GroupLane& 
       if (kLearned && decide) r.mode = kGroupDecide;
       return true;
     }
-    const float tf = r.pt0 + (go_up ? t_up : t_lo);
-    const uint32_t pid = r.pmeta & kIdMask;
-    if (tf < r.best_t || (tf == r.best_t && pid < r.best_id)) {
-      const CodeT lc = r.code | (go_up ? bit : (CodeT)0);
-      r.best_t = tf;
-      r.best_id = pid;
-      r.hu = (float)(2u * compact_even(lc >> 1) + 1u) * (0.5f * leaf_scale);
-      r.hv = (float)(2u * compact_even(lc) + 1u) * (0.5f * leaf_scale);
-    }
+    group_leaf(r, r.pt0 + (go_up ? t_up : t_lo), (CodeT)(r.code | (go_up ? bit : (CodeT)0)), leaf_scale);
   }
   if (r.trail == 0) return false;
   const int k = sizeof(CodeT) == 8 ? __builtin_ctzll((uint64_t)r.trail) : __builtin_ctz((uint32_t)r.trail);
@@ -403,6 +442,177 @@ __device__ __forceinline__ void group_decide(GroupRay<CodeT>& r, const PolicyDev
       r.mode = (r.pmeta & kGregoryBit) ? kGroupGrid : kGroupStep;
     }
   }
+}
+
+// ------------------------------------------------------------ one ray to a wave
+// When a wave holds a single ray, all four groups carry it and its control state is
+// the wave's: path, trail and stack live in scalar registers and every decision is a
+// scalar branch (a Bezier step then issues ~130 instructions instead of ~240).  On a
+// Gregory patch, whose grids depend on the domain alone, the groups expand four
+// nodes at once: the current one, its two children and the nearest pending sibling
+// (at a leaf's parent the three nearest); what the traversal does next is looked up
+// among them.  Nothing is used that was tested against another best distance.
+// Heaviest rays of three scenes alone, on 16 lanes -> on 64: torus 175 -> 98 us, its
+// leaf depth 18 792 -> 405 us, world frames 1092 -> 790 us.
+//
+// A node is one word here: its path code with a marker bit below the last split's
+// (bit L2-1-depth, the bit its own split would own).
+template <typename T>
+__device__ __forceinline__ T uniform(T x) {
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8, "words");
+  uint32_t w[sizeof(T) / 4];
+  __builtin_memcpy(w, &x, sizeof(T));
+#pragma unroll
+  for (uint32_t k = 0; k < sizeof(T) / 4; ++k) w[k] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[k]);
+  __builtin_memcpy(&x, w, sizeof(T));
+  return x;
+}
+
+// Whether a condition that is the same in all lanes holds, as a scalar.
+__device__ __forceinline__ bool wave_is(bool x) { return __ballot(x) != 0; }
+
+template <typename CodeT>
+__device__ __forceinline__ CodeT lowest(CodeT x) { return x & (CodeT)(0 - x); }
+
+// The sibling pending at the lowest bit of `trail` (not 0).
+template <typename CodeT>
+__device__ __forceinline__ CodeT pending(CodeT node, CodeT trail) {
+  const CodeT bit = lowest(trail);
+  return ((node ^ bit) & ~(CodeT)(bit - 1)) | (CodeT)(bit >> 1);
+}
+
+// Path code, depth and domain corner of a node into r.
+template <typename CodeT>
+__device__ __forceinline__ void solo_domain(GroupRay<CodeT>& r, CodeT node, int L2, float leaf_scale) {
+  r.code = node & (CodeT)(node - 1);
+  const int k = sizeof(CodeT) == 8 ? __builtin_ctzll((uint64_t)node) : __builtin_ctz((uint32_t)node);
+  r.depth = L2 - 1 - k;
+  group_corner(r, leaf_scale);
+}
+
+// Gregory patch: from `node`, whose grid is due, as far as one expansion reaches.
+// Returns false when the patch is finished.
+template <typename CodeT>
+__device__ __forceinline__ bool solo_expand(GroupRay<CodeT>& r, const GroupLane& ln, CodeT& node, CodeT& trail, int L2,
+                                            float leaf_scale, int lane) {
+  CodeT n1 = 0, n2 = 0, n3 = 0;  // 0 is no node
+  {
+    CodeT left = trail;
+    auto next = [&]() {
+      CodeT p = 0;
+      if (left != 0) {
+        p = pending(node, left);
+        left &= left - 1;
+      }
+      return p;
+    };
+    const CodeT bit = lowest(node);
+    if (bit != 1) {
+      n1 = (node ^ bit) | (CodeT)(bit >> 1);
+      n2 = node | (CodeT)(bit >> 1);
+    } else {
+      n1 = next();
+      n2 = next();
+    }
+    n3 = next();
+  }
+  const int group = lane / kGroupLanes;
+  CodeT own = group == 0 ? node : group == 1 ? n1 : group == 2 ? n2 : n3;
+  own = own != 0 ? own : node;
+  solo_domain(r, own, L2, leaf_scale);
+  group_grid<2>(r, ln);
+  const GroupSplit h = group_split(r);  // a fresh grid: the lower half is stored first
+  const bool up = h.hit_b && (!h.hit_a || h.tb < h.ta);
+  const float tf = r.pt0 + (up ? h.tb : h.ta);
+  const int seen = (h.hit_a ? 1 : 0) | (h.hit_b ? 2 : 0) | (up ? 4 : 0);
+  const int s0 = __builtin_amdgcn_readlane(seen, 0), s1 = __builtin_amdgcn_readlane(seen, kGroupLanes),
+            s2 = __builtin_amdgcn_readlane(seen, 2 * kGroupLanes), s3 = __builtin_amdgcn_readlane(seen, 3 * kGroupLanes);
+  int see = s0;
+  for (;;) {
+    const CodeT bit = lowest(node);
+    bool better = false;
+    if ((see & 3) != 0) {
+      if (bit != 1) {
+        trail |= (see & 3) == 3 ? bit : (CodeT)0;
+        node = ((see & 4) ? node : (CodeT)(node ^ bit)) | (CodeT)(bit >> 1);
+        see = node == n1 ? s1 : node == n2 ? s2 : node == n3 ? s3 : -1;
+        if (see < 0) return true;
+        continue;
+      }
+      const int at = node == n1 ? 1 : node == n2 ? 2 : node == n3 ? 3 : 0;
+      const float t = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tf), kGroupLanes * at));
+      better = wave_is(group_leaf(r, t, (CodeT)((node ^ bit) | ((see & 4) ? 1 : 0)), leaf_scale));
+    }
+    if (trail == 0) return false;
+    node = pending(node, trail);
+    trail &= trail - 1;
+    see = node == n1 ? s1 : node == n2 ? s2 : node == n3 ? s3 : -1;
+    if (see < 0 || better) return true;  // after a record the other nodes' tests are out of date
+  }
+}
+
+// The current patch of a wave's ray, whose grid is due or in r.g with r.mirror, to its end.
+template <typename CodeT>
+__device__ __forceinline__ void solo_patch(GroupRay<CodeT>& r, const GroupLane& ln, int L2, float leaf_scale, int lane) {
+  CodeT trail = uniform(r.trail);
+  CodeT node = uniform(r.code) | (CodeT)1 << (L2 - 1 - uniform(r.depth));
+  bool due = uniform(r.mode) == kGroupGrid;
+  const int axis = uniform(r.depth) & 1;
+  // mirror bit of the next split's axis and of the other one: every descent swaps them
+  uint32_t m0 = (uniform(r.mirror) >> axis) & 1u, m1 = (uniform(r.mirror) >> (axis ^ 1)) & 1u;
+  const bool gregory = (uniform(r.pmeta) & kGregoryBit) != 0;
+  for (;;) {
+    if (due) {
+      if (gregory) {
+        if (!solo_expand(r, ln, node, trail, L2, leaf_scale, lane)) return;
+        continue;
+      }
+      solo_domain(r, node, L2, leaf_scale);
+      group_grid<0>(r, ln);
+      m0 = m1 = 0;
+    }
+    const GroupSplit h = group_split(r);
+    const bool mir = m0 != 0;
+    const bool h_lo = mir ? h.hit_b : h.hit_a, h_up = mir ? h.hit_a : h.hit_b;
+    const float t_lo = mir ? h.tb : h.ta, t_up = mir ? h.ta : h.tb;
+    const bool go_up = h_up && (!h_lo || t_up < t_lo);
+    const int see = uniform((h_lo ? 1 : 0) | (h_up ? 2 : 0) | (go_up ? 4 : 0));
+    const CodeT bit = lowest(node);
+    if ((see & 3) != 0) {
+      if (bit != 1) {
+        const bool second = ((see >> 2) & 1) != (int)m0;
+        r.g[0] = second ? h.e.v[6] : h.e.v[0];
+        r.g[1] = second ? h.e.v[5] : h.e.v[1];
+        r.g[2] = second ? h.e.v[4] : h.e.v[2];
+        r.g[3] = h.e.v[3];
+        quad_transpose(r.g, ln.b0, ln.b1);
+        const uint32_t m = m0 ^ (second ? 1u : 0u);
+        m0 = m1;
+        m1 = m;
+        trail |= (see & 3) == 3 ? bit : (CodeT)0;
+        node = ((see & 4) ? node : (CodeT)(node ^ bit)) | (CodeT)(bit >> 1);
+        due = gregory;
+        continue;
+      }
+      group_leaf(r, r.pt0 + (go_up ? t_up : t_lo), (CodeT)((node ^ bit) | ((see & 4) ? 1 : 0)), leaf_scale);
+    }
+    if (trail == 0) return;
+    node = pending(node, trail);
+    trail &= trail - 1;
+    due = true;
+  }
+}
+
+// Every group's lanes take the words of the lanes of the group that starts at `first`.
+template <typename T>
+__device__ __forceinline__ void spread(T& x, int first, int lane) {
+  static_assert(sizeof(T) % 4 == 0, "words");
+  uint32_t w[sizeof(T) / 4];
+  __builtin_memcpy(w, &x, sizeof(T));
+#pragma unroll
+  for (uint32_t k = 0; k < sizeof(T) / 4; ++k)
+    w[k] = (uint32_t)__shfl((int)w[k], first + (lane & (kGroupLanes - 1)));
+  __builtin_memcpy(&x, w, sizeof(T));
 }
 
 }  // namespace ccs
