@@ -96,25 +96,6 @@ __device__ __forceinline__ void write_hit(const BatchTable& bt, uint32_t* __rest
   }
 }
 
-// kLearned: the child-ordering network picks the u-half at decision nodes
-// (policy.h).  The lane first descends the closest-first way, stores the
-// node's policy inputs and waits in DECIDE; the wave then runs the network for
-// all waiting lanes on the matrix cores.  A lane whose network prefers the other
-// u-half flips that level's path bit (its trail bit stays set, so the
-// closest-first half becomes the pending sibling) and has its grid recomputed;
-// one split later it takes the v-half of the network's top grandchild when both
-// v-halves are hit.
-// Three waves per SIMD (at most 168 VGPRs): the closest-first variant fits by
-// itself; the learned variant is held to it (a few loop-invariant values of the
-// ray-fetch and leaf-record paths then live in scratch instead of registers).
-//
-// kSingle (the ablation of Sec. 3.3's two-box test, closest-first kernels only):
-// a step tests only the box of the current domain (the hull of its grid, grown by
-// its own displacement) and, when it is hit above the leaf depth, splits and
-// enters the lower half with the upper one pending; a missed box backtracks, and
-// a hit leaf box is recorded at its own entry distance.  No distance orders the
-// halves, and every pending half costs a grid recompute.
-
 // A wave's single ray to its end; every value of r is the same in all groups.
 template <int kStride, typename CodeT>
 __device__ __forceinline__ void solo_loop(GroupRay<CodeT>& r, const GroupLane& ln, const BatchTable& bt, int L2,
@@ -229,6 +210,24 @@ __device__ __forceinline__ void group_open_ray(GroupRay<CodeT>& r, const GroupLa
   group_set_ray(r, ln, ro, rd);
 }
 
+// kLearned: the child-ordering network picks the u-half at decision nodes
+// (policy.h).  The lane first descends the closest-first way, stores the
+// node's policy inputs and waits in DECIDE; the wave then runs the network for
+// all waiting lanes on the matrix cores.  A lane whose network prefers the other
+// u-half flips that level's path bit (its trail bit stays set, so the
+// closest-first half becomes the pending sibling) and has its grid recomputed;
+// one split later it takes the v-half of the network's top grandchild when both
+// v-halves are hit.
+// Three waves per SIMD (at most 168 VGPRs): the closest-first variant fits by
+// itself; the learned variant is held to it (a few loop-invariant values of the
+// ray-fetch and leaf-record paths then live in scratch instead of registers).
+//
+// kSingle (the ablation of Sec. 3.3's two-box test, closest-first kernels only):
+// a step tests only the box of the current domain (the hull of its grid, grown by
+// its own displacement) and, when it is hit above the leaf depth, splits and
+// enters the lower half with the upper one pending; a missed box backtracks, and
+// a hit leaf box is recorded at its own entry distance.  No distance orders the
+// halves, and every pending half costs a grid recompute.
 template <bool kStats, bool kLearned, bool kSingle, typename CodeT>
 __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTable& bt, uint32_t* __restrict__ counters,
                                            const LaunchParams& lp) {
@@ -438,7 +437,12 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
     // and 3r+2 (helpers, whatever their own mode), each with the arithmetic of
     // calc_points_and_d for its component, and pulls them back.  At most
     // kGridOwners lanes are served per phase; the others wait for the next one.
-    if (mg != 0 && ((uint32_t)__popcll(mg) >= lp.grid_min || ms == 0)) {
+    // Once no ray will refill the lanes, waiting for company costs more than it saves:
+    // from then on two waiting lanes run the phase (a two-bounce path at 1280x720 1846 ->
+    // 1775 us, the torus' 32k rays 327 -> 317, the learned order 1056 -> 1040; launches
+    // that refill for most of their time unchanged; 1 and 4 are as good, 16 loses 15 %).
+    const uint32_t grid_min = drained && lp.grid_min > 2u ? 2u : lp.grid_min;
+    if (mg != 0 && ((uint32_t)__popcll(mg) >= grid_min || ms == 0)) {
       const uint32_t n_wait = (uint32_t)__popcll(mg);
       const uint32_t n_own = n_wait < kGridOwners ? n_wait : kGridOwners;
       const uint32_t rank = (uint32_t)__popcll(mg & ((1ull << lane) - 1ull));
