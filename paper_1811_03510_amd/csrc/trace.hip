@@ -55,6 +55,8 @@ constexpr int kBlock = 64;
 // 1280x720; at 1, 2 and 4 the torus' 32k rays take 452, 405 and 387 us against
 // 290, the path 2291, 2108 and 2035 against 1860 us.
 constexpr int kTailRays = 8;
+// lanes that stand at a candidate before the wave sets them up, in patch frames
+constexpr uint32_t kSetupMin = 8;
 constexpr int kSoloWaves = 5;  // waves per SIMD of the wave-per-ray kernel
 constexpr uint32_t kGridOwners = kBlock / 3;  // lanes whose grids one recompute phase serves
 
@@ -272,16 +274,17 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
 
   for (;;) {
     uint64_t mf = __ballot(mode == kFetch);
-    uint64_t mt = __ballot(mode == kTraverse);
+    uint64_t mt = __ballot(mode == kTraverse && cur >= 0);
+    uint64_t mc = __ballot(mode == kTraverse && cur < 0);  // stands at a candidate
     uint64_t ms = __ballot(mode == kStep);
     uint64_t mg = __ballot(mode == kGrid);
     if (kLearned) ms |= __ballot(mode == kDecide);  // lanes that will step once decided
     if (kTail) {
-      busy = mt | ms | mg;
+      busy = mt | mc | ms | mg;
       few = drained && __popcll(busy) <= kTailRays;
       // learned order: not while a node waits for the network with its values in LDS
       if (few && (!kLearned || __ballot(mode == kDecide) == 0)) break;
-    } else if ((mf | mt | ms | mg) == 0) {
+    } else if ((mf | mt | mc | ms | mg) == 0) {
       break;
     }
 
@@ -291,7 +294,7 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
     // leave earlier; results do not depend on it.
     __builtin_amdgcn_s_setprio(1);
     // ------------------------------------------------------------ fetch rays
-    if (mf != 0 && ((uint32_t)__popcll(mf) >= lp.fetch_min || (mt | ms | mg) == 0)) {
+    if (mf != 0 && ((uint32_t)__popcll(mf) >= lp.fetch_min || (mt | mc | ms | mg) == 0)) {
       uint32_t base = 0;
       if (!kLearned && lp.queue == nullptr) {  // one fetch per wave takes the whole launch
         base = drained ? n : blockIdx.x * lp.lanes;
@@ -342,61 +345,15 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
           }
         }
       }
-      mt = __ballot(mode == kTraverse);
+      mt = __ballot(mode == kTraverse && cur >= 0);
     }
 
     __builtin_amdgcn_s_setprio(2);
     // ------------------------------------------- traverse to the next candidate
-    if (mt != 0 && ((uint32_t)__popcll(mt) >= lp.traverse_min || (ms | mg) == 0)) {
+    if (mt != 0 && ((uint32_t)__popcll(mt) >= lp.traverse_min || (mc | ms | mg) == 0)) {
       // at most traverse_steps node visits per phase: lanes still walking keep their
       // place and continue next time, so one lane's long walk does not hold the wave
-      for (uint32_t it = 0; mode == kTraverse && it < lp.traverse_steps; ++it) {
-        if (cur < 0) {  // candidate patch: set up Alg. 3 at the root
-          if (kStats) cnt.cand++;
-          rec_idx = (uint32_t)(~cur);
-          const float* rec = recs + (size_t)rec_idx * kRecFloats;
-          const float4 meta = reinterpret_cast<const float4*>(rec)[15];
-          pmeta = __float_as_uint(meta.w);
-          if (s.frames) {
-            // patch-local frame: origin and direction mapped by the patch's rows
-            const float4* fr = s.frames + (size_t)bt.frame[batch_of(bt, rid)] * s.frame_frames_f4 + 3 * (size_t)rec_idx;
-            const float4 r0 = fr[0], r1 = fr[1], r2 = fr[2];
-            float pdx, pdy, pdz;
-            patch_frame_rows(meta, r0, r1, r2, wr.ox, wr.oy, wr.oz, s_dir[0][lane], s_dir[1][lane], s_dir[2][lane],
-                             wr.tmin, pox, poy, poz, pdx, pdy, pdz, ptmin, pt0);
-            pix = safe_inv(pdx);
-            piy = safe_inv(pdy);
-            piz = safe_inv(pdz);
-            // boxes grown by the pad on all sides: the low planes move by -pad through the
-            // origin (o + pad), the high planes by +pad through d + 2 pad
-            pox += r0.w;
-            poy += r0.w;
-            poz += r0.w;
-            pad2 = 2.0f * r0.w;
-          } else {
-            patch_frame(meta, wr.ox, wr.oy, wr.oz, s_dir[0][lane], s_dir[1][lane], s_dir[2][lane], wr.tmin, pox,
-                        poy, poz, ptmin, pt0);
-            pix = wr.ix;
-            piy = wr.iy;
-            piz = wr.iz;
-          }
-          code = trail = 0;
-          mirror = 0;
-          depth = 0;
-          if (pmeta & kGregoryBit) {
-            if (kStats) cnt.cand_greg++;
-            mode = kGrid;
-          } else {
-            PatchPts P;
-            load_grid(rec, P, false);
-            orient(P.x, false, G.x);
-            orient(P.y, false, G.y);
-            orient(P.z, false, G.z);
-            dx = dy = dz = pad2;
-            mode = kStep;
-          }
-          break;
-        }
+      for (uint32_t it = 0; mode == kTraverse && cur >= 0 && it < lp.traverse_steps; ++it) {
         if (kStats) cnt.node++;
         const float4* nd = nodes + 4 * (size_t)cur;
         const float4 a = nd[0], b = nd[1], c = nd[2], e = nd[3];
@@ -425,6 +382,63 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
           mode = kFetch;
         }
       }
+      mc = __ballot(mode == kTraverse && cur < 0);
+    }
+
+    // --------------------------------------------- set up candidates in a batch
+    // In patch frames the mapping is 87 vector instructions, 49 of them FP64, for the 4 of
+    // 64 lanes that find a candidate in an iteration: lanes wait until kSetupMin do.
+    // 2M primary and 2M secondary rays on 1M patches 5.92 -> 5.58 ms (at 1, 4, 12 lanes:
+    // 5.80, 5.67, 5.60).  Not in world frames, where it is 40 instructions (460k rays on
+    // 200 objects 1.85 -> 1.89 ms at 8), and not once the queue is empty (as grid_min).
+    const uint32_t setup_min = s.frames != nullptr && !drained ? kSetupMin : 1u;
+    if (mc != 0 && ((uint32_t)__popcll(mc) >= setup_min || (ms | mg) == 0)) {
+      if (mode == kTraverse && cur < 0) {  // candidate patch: set up Alg. 3 at the root
+        if (kStats) cnt.cand++;
+        rec_idx = (uint32_t)(~cur);
+        const float* rec = recs + (size_t)rec_idx * kRecFloats;
+        const float4 meta = reinterpret_cast<const float4*>(rec)[15];
+        pmeta = __float_as_uint(meta.w);
+        if (s.frames) {
+          // patch-local frame: origin and direction mapped by the patch's rows
+          const float4* fr = s.frames + (size_t)bt.frame[batch_of(bt, rid)] * s.frame_frames_f4 + 3 * (size_t)rec_idx;
+          const float4 r0 = fr[0], r1 = fr[1], r2 = fr[2];
+          float pdx, pdy, pdz;
+          patch_frame_rows(meta, r0, r1, r2, wr.ox, wr.oy, wr.oz, s_dir[0][lane], s_dir[1][lane], s_dir[2][lane],
+                           wr.tmin, pox, poy, poz, pdx, pdy, pdz, ptmin, pt0);
+          pix = safe_inv(pdx);
+          piy = safe_inv(pdy);
+          piz = safe_inv(pdz);
+          // boxes grown by the pad on all sides: the low planes move by -pad through the
+          // origin (o + pad), the high planes by +pad through d + 2 pad
+          pox += r0.w;
+          poy += r0.w;
+          poz += r0.w;
+          pad2 = 2.0f * r0.w;
+        } else {
+          patch_frame(meta, wr.ox, wr.oy, wr.oz, s_dir[0][lane], s_dir[1][lane], s_dir[2][lane], wr.tmin, pox,
+                      poy, poz, ptmin, pt0);
+          pix = wr.ix;
+          piy = wr.iy;
+          piz = wr.iz;
+        }
+        code = trail = 0;
+        mirror = 0;
+        depth = 0;
+        if (pmeta & kGregoryBit) {
+          if (kStats) cnt.cand_greg++;
+          mode = kGrid;
+        } else {
+          PatchPts P;
+          load_grid(rec, P, false);
+          orient(P.x, false, G.x);
+          orient(P.y, false, G.y);
+          orient(P.z, false, G.z);
+          dx = dy = dz = pad2;
+          mode = kStep;
+        }
+      }
+
       ms = __ballot(mode == kStep);
       if (kLearned) ms |= __ballot(mode == kDecide);
       mg = __ballot(mode == kGrid);
