@@ -55,6 +55,8 @@ constexpr int kBlock = 64;
 // 1280x720; at 1, 2 and 4 the torus' 32k rays take 452, 405 and 387 us against
 // 290, the path 2291, 2108 and 2035 against 1860 us.
 constexpr int kTailRays = 8;
+// lanes that can split again for the wave to split twice in a turn
+constexpr int kSplitAgain = 16;
 // lanes that stand at a candidate before the wave sets them up, in patch frames
 constexpr uint32_t kSetupMin = 8;
 constexpr int kSoloWaves = 5;  // waves per SIMD of the wave-per-ray kernel
@@ -556,136 +558,143 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
       }
     }
 
-    // -------------------------------------------------- one subdivision step
-    if (mode == kStep) {
-      if (kStats) cnt.split++;
-      bool backtrack;
-      if constexpr (kSingle) {
-        // the box of the current domain only: its grid's hull, the maximum side grown
-        // by the domain's own displacement
-        SlabPair one = {ptmin, __builtin_inff(), ptmin, __builtin_inff()};
-        grid_fold(G.x, pox, pix, dx, one);
-        grid_fold(G.y, poy, piy, dy, one);
-        grid_fold(G.z, poz, piz, dz, one);
-        const float cap = (best_t - pt0) + (fabsf(best_t) + fabsf(pt0)) * 0x1p-22f;
-        const bool hit = one.na <= fminf(widen_far(one.fa), cap);
-        backtrack = true;
-        if (hit && depth == L2) {
-          const float tf = pt0 + one.na;
-          const uint32_t pid = pmeta & kIdMask;
-          if (tf < best_t || (tf == best_t && pid < best_id)) {
-            best_t = tf;
-            best_id = pid;
-            s_uv[0][lane] = (float)(2u * compact_even(code >> 1) + 1u) * (0.5f * leaf_scale);
-            s_uv[1][lane] = (float)(2u * compact_even(code) + 1u) * (0.5f * leaf_scale);
-            if (kStats) cnt.leaf++;
+    // ------------------------------------------- one subdivision step, or two
+    // A lane in a Bezier patch goes on to its next split at once: the other phases of
+    // a turn cost twice a split, and about 20 of the 34 lanes that split can split again.
+    // 2M primary and 2M secondary rays on 1M patches 5.53 -> 5.30 ms, 24,001 rays on each
+    // of 16 frames 970 -> 909 us; at 8 lanes 5.33, up to three or four splits 5.34, 5.32.
+    for (bool again = false;; again = true) {
+      if (mode == kStep) {
+        if (kStats) cnt.split++;
+        bool backtrack;
+        if constexpr (kSingle) {
+          // the box of the current domain only: its grid's hull, the maximum side grown
+          // by the domain's own displacement
+          SlabPair one = {ptmin, __builtin_inff(), ptmin, __builtin_inff()};
+          grid_fold(G.x, pox, pix, dx, one);
+          grid_fold(G.y, poy, piy, dy, one);
+          grid_fold(G.z, poz, piz, dz, one);
+          const float cap = (best_t - pt0) + (fabsf(best_t) + fabsf(pt0)) * 0x1p-22f;
+          const bool hit = one.na <= fminf(widen_far(one.fa), cap);
+          backtrack = true;
+          if (hit && depth == L2) {
+            const float tf = pt0 + one.na;
+            const uint32_t pid = pmeta & kIdMask;
+            if (tf < best_t || (tf == best_t && pid < best_id)) {
+              best_t = tf;
+              best_id = pid;
+              s_uv[0][lane] = (float)(2u * compact_even(code >> 1) + 1u) * (0.5f * leaf_scale);
+              s_uv[1][lane] = (float)(2u * compact_even(code) + 1u) * (0.5f * leaf_scale);
+              if (kStats) cnt.leaf++;
+            }
+          } else if (hit) {
+            // split and enter the lower half, the upper one pending
+            const int axis = depth & 1;
+            const bool second = ((mirror >> axis) & 1u) != 0;  // the lower half is register-second when mirrored
+            Row7 ex[4], ey[4], ez[4];
+            SlabPair unused = {0.0f, 0.0f, 0.0f, 0.0f};
+            split_fold(G.x, 0.0f, 1.0f, 0.0f, ex, unused);
+            split_fold(G.y, 0.0f, 1.0f, 0.0f, ey, unused);
+            split_fold(G.z, 0.0f, 1.0f, 0.0f, ez, unused);
+            take_half(ex, second, G.x);
+            take_half(ey, second, G.y);
+            take_half(ez, second, G.z);
+            trail |= (CodeT)1 << (L2 - 1 - depth);
+            if (second) mirror ^= (1u << axis);
+            depth++;
+            backtrack = false;
+            if (pmeta & kGregoryBit) mode = kGrid;  // the child's own bound (Alg. 2 on its domain)
           }
-        } else if (hit) {
-          // split and enter the lower half, the upper one pending
-          const int axis = depth & 1;
-          const bool second = ((mirror >> axis) & 1u) != 0;  // the lower half is register-second when mirrored
+        } else {
+          // split each component and fold its two child boxes into the slab test at once
           Row7 ex[4], ey[4], ez[4];
-          SlabPair unused = {0.0f, 0.0f, 0.0f, 0.0f};
-          split_fold(G.x, 0.0f, 1.0f, 0.0f, ex, unused);
-          split_fold(G.y, 0.0f, 1.0f, 0.0f, ey, unused);
-          split_fold(G.z, 0.0f, 1.0f, 0.0f, ez, unused);
+          SlabPair sp2 = {ptmin, __builtin_inff(), ptmin, __builtin_inff()};
+          split_fold(G.x, pox, pix, dx, ex, sp2);
+          split_fold(G.y, poy, piy, dy, ey, sp2);
+          split_fold(G.z, poz, piz, dz, ez, sp2);
+          // the best distance in the patch frame: best_t - pt0 carries the rounding of
+          // best_t = pt0 + t and of the difference (each at most 2^-24 relative), so it
+          // is widened by twice their bound and a leaf at the best distance is never pruned
+          const float cap = (best_t - pt0) + (fabsf(best_t) + fabsf(pt0)) * 0x1p-22f;
+          const float fa = fminf(widen_far(sp2.fa), cap), fb = fminf(widen_far(sp2.fb), cap);
+          const bool ha = sp2.na <= fa, hb = sp2.nb <= fb;
+          const float ta = sp2.na, tb = sp2.nb;
+          const int axis = depth & 1;
+          const bool mir = ((mirror >> axis) & 1u) != 0;
+          const bool h_lo = mir ? hb : ha, h_up = mir ? ha : hb;
+          const float t_lo = mir ? tb : ta, t_up = mir ? ta : tb;
+          bool go_up = h_up && (!h_lo || t_up < t_lo);
+          const CodeT bit = (CodeT)1 << (L2 - 1 - depth);
+          const uint32_t mirror0 = mirror;
+          bool decide = false;
+          if (kLearned) {
+            // v-split after a decision: the network's v-half when both are hit (not at the
+            // leaf pair, which is resolved by distance)
+            if ((vpref & 1u) && axis == 1 && ha && hb && depth != L2 - 1) go_up = (vpref & 2u) != 0;
+            vpref = 0;
+            decide = axis == 0 && ha && hb;
+          }
+          // the chosen half replaces the grid on every path: when the lane backtracks or
+          // leaves the patch instead, the grid is rebuilt before it is read again
+          const bool second = go_up != mir;
+          if (kLearned && decide) {
+            // the node's corners in storage order (0,0), (3,0), (0,3), (3,3) and its slab
+            // results, kept for the decision (formed there, off this phase's registers)
+            const float sx[4] = {ex[0].v[0], ex[0].v[6], ex[3].v[0], ex[3].v[6]};
+            const float sy[4] = {ey[0].v[0], ey[0].v[6], ey[3].v[0], ey[3].v[6]};
+            const float sz[4] = {ez[0].v[0], ez[0].v[6], ez[3].v[0], ez[3].v[6]};
+            policy_store_node(s_feat, lane, sx, sy, sz, sp2);
+            s_mirror[lane] = (uint8_t)mirror0;
+          }
           take_half(ex, second, G.x);
           take_half(ey, second, G.y);
           take_half(ez, second, G.z);
-          trail |= (CodeT)1 << (L2 - 1 - depth);
-          if (second) mirror ^= (1u << axis);
-          depth++;
-          backtrack = false;
-          if (pmeta & kGregoryBit) mode = kGrid;  // the child's own bound (Alg. 2 on its domain)
-        }
-      } else {
-        // split each component and fold its two child boxes into the slab test at once
-        Row7 ex[4], ey[4], ez[4];
-        SlabPair sp2 = {ptmin, __builtin_inff(), ptmin, __builtin_inff()};
-        split_fold(G.x, pox, pix, dx, ex, sp2);
-        split_fold(G.y, poy, piy, dy, ey, sp2);
-        split_fold(G.z, poz, piz, dz, ez, sp2);
-        // the best distance in the patch frame: best_t - pt0 carries the rounding of
-        // best_t = pt0 + t and of the difference (each at most 2^-24 relative), so it
-        // is widened by twice their bound and a leaf at the best distance is never pruned
-        const float cap = (best_t - pt0) + (fabsf(best_t) + fabsf(pt0)) * 0x1p-22f;
-        const float fa = fminf(widen_far(sp2.fa), cap), fb = fminf(widen_far(sp2.fb), cap);
-        const bool ha = sp2.na <= fa, hb = sp2.nb <= fb;
-        const float ta = sp2.na, tb = sp2.nb;
-        const int axis = depth & 1;
-        const bool mir = ((mirror >> axis) & 1u) != 0;
-        const bool h_lo = mir ? hb : ha, h_up = mir ? ha : hb;
-        const float t_lo = mir ? tb : ta, t_up = mir ? ta : tb;
-        bool go_up = h_up && (!h_lo || t_up < t_lo);
-        const CodeT bit = (CodeT)1 << (L2 - 1 - depth);
-        const uint32_t mirror0 = mirror;
-        bool decide = false;
-        if (kLearned) {
-          // v-split after a decision: the network's v-half when both are hit (not at the
-          // leaf pair, which is resolved by distance)
-          if ((vpref & 1u) && axis == 1 && ha && hb && depth != L2 - 1) go_up = (vpref & 2u) != 0;
-          vpref = 0;
-          decide = axis == 0 && ha && hb;
-        }
-        // the chosen half replaces the grid on every path: when the lane backtracks or
-        // leaves the patch instead, the grid is rebuilt before it is read again
-        const bool second = go_up != mir;
-        if (kLearned && decide) {
-          // the node's corners in storage order (0,0), (3,0), (0,3), (3,3) and its slab
-          // results, kept for the decision (formed there, off this phase's registers)
-          const float sx[4] = {ex[0].v[0], ex[0].v[6], ex[3].v[0], ex[3].v[6]};
-          const float sy[4] = {ey[0].v[0], ey[0].v[6], ey[3].v[0], ey[3].v[6]};
-          const float sz[4] = {ez[0].v[0], ez[0].v[6], ez[3].v[0], ez[3].v[6]};
-          policy_store_node(s_feat, lane, sx, sy, sz, sp2);
-          s_mirror[lane] = (uint8_t)mirror0;
-        }
-        take_half(ex, second, G.x);
-        take_half(ey, second, G.y);
-        take_half(ez, second, G.z);
-        backtrack = !(ha || hb);
-        if (!backtrack) {
-          if (depth == L2 - 1) {
-            const float tf = pt0 + (go_up ? t_up : t_lo);
-            const uint32_t pid = pmeta & kIdMask;
-            if (tf < best_t || (tf == best_t && pid < best_id)) {
-              const CodeT lc = code | (go_up ? bit : (CodeT)0);
-              best_t = tf;
-              best_id = pid;
-              s_uv[0][lane] = (float)(2u * compact_even(lc >> 1) + 1u) * (0.5f * leaf_scale);
-              s_uv[1][lane] = (float)(2u * compact_even(lc) + 1u) * (0.5f * leaf_scale);
-              if (kStats) cnt.leaf++;
+          backtrack = !(ha || hb);
+          if (!backtrack) {
+            if (depth == L2 - 1) {
+              const float tf = pt0 + (go_up ? t_up : t_lo);
+              const uint32_t pid = pmeta & kIdMask;
+              if (tf < best_t || (tf == best_t && pid < best_id)) {
+                const CodeT lc = code | (go_up ? bit : (CodeT)0);
+                best_t = tf;
+                best_id = pid;
+                s_uv[0][lane] = (float)(2u * compact_even(lc >> 1) + 1u) * (0.5f * leaf_scale);
+                s_uv[1][lane] = (float)(2u * compact_even(lc) + 1u) * (0.5f * leaf_scale);
+                if (kStats) cnt.leaf++;
+              }
+              backtrack = true;
+            } else {
+              if (ha && hb) trail |= bit;
+              if (go_up) code |= bit;
+              if (second) mirror ^= (1u << axis);
+              depth++;
+              if (pmeta & kGregoryBit) mode = kGrid;  // Alg. 3 recomputes a Gregory grid at every node
+              if (kLearned && decide) mode = kDecide;
             }
-            backtrack = true;
+          }
+        }
+        if (backtrack) {
+          if (trail != 0) {
+            const int b = sizeof(CodeT) == 8 ? __builtin_ctzll((uint64_t)trail) : __builtin_ctz((uint32_t)trail);
+            const CodeT tb_bit = (CodeT)1 << b;
+            trail ^= tb_bit;
+            code = (code ^ tb_bit) & ~(tb_bit - 1);
+            depth = L2 - b;
+            mode = kGrid;
+            if (kStats) cnt.backtrack++;
           } else {
-            if (ha && hb) trail |= bit;
-            if (go_up) code |= bit;
-            if (second) mirror ^= (1u << axis);
-            depth++;
-            if (pmeta & kGregoryBit) mode = kGrid;  // Alg. 3 recomputes a Gregory grid at every node
-            if (kLearned && decide) mode = kDecide;
+            if (sp > 0) {  // next candidate from the stack
+              --sp;
+              cur = stack[sp * kBlock + lane];
+              mode = kTraverse;
+            } else {  // ray done
+              write_hit<kStats>(bt, counters, rid, best_t, best_id, s_uv[0][lane], s_uv[1][lane], cnt);
+              mode = kFetch;
+            }
           }
         }
       }
-      if (backtrack) {
-        if (trail != 0) {
-          const int b = sizeof(CodeT) == 8 ? __builtin_ctzll((uint64_t)trail) : __builtin_ctz((uint32_t)trail);
-          const CodeT tb_bit = (CodeT)1 << b;
-          trail ^= tb_bit;
-          code = (code ^ tb_bit) & ~(tb_bit - 1);
-          depth = L2 - b;
-          mode = kGrid;
-          if (kStats) cnt.backtrack++;
-        } else {
-          if (sp > 0) {  // next candidate from the stack
-            --sp;
-            cur = stack[sp * kBlock + lane];
-            mode = kTraverse;
-          } else {  // ray done
-            write_hit<kStats>(bt, counters, rid, best_t, best_id, s_uv[0][lane], s_uv[1][lane], cnt);
-            mode = kFetch;
-          }
-        }
-      }
+      if (again || __popcll(__ballot(mode == kStep)) < kSplitAgain) break;
     }
   }
   // The wave's last rays, 16 lanes each (trace_group.h).  Their states go through
