@@ -214,7 +214,8 @@ ccs_status ccs_intersect_counted(const ccs_scene* scene, const ccs_ray* rays, ui
  * carry a ray through fetch, traversal, subdivision steps and grid
  * recomputations; a wave runs the fetch, traversal or recompute phase only when
  * at least the given number of its 64 lanes waits for it (or nothing else can
- * run), so that these divergent phases run on filled waves. */
+ * run), so that these divergent phases run on filled waves.  Once every ray has
+ * been taken, the traversal phase runs for any lane and the recompute phase for two. */
 typedef struct ccs_launch_params {
   uint32_t waves_per_cu;   /* resident waves per compute unit; 0 = as many as fit */
   uint32_t fetch_min;      /* 1..64 lanes waiting for a new ray */
@@ -225,7 +226,7 @@ typedef struct ccs_launch_params {
 } ccs_launch_params;
 
 /* Sets the launch configuration used by later ccs_intersect* calls on the
- * scene.  Defaults: {0, 16, 1, 8, 3, 8}.  CCS_ERR_INVALID_ARG for thresholds
+ * scene.  Defaults: {0, 16, 16, 8, 3, 8}.  CCS_ERR_INVALID_ARG for thresholds
  * outside [1, 64].  Not synchronized with calls in flight on other threads. */
 ccs_status ccs_scene_set_launch(ccs_scene* scene, const ccs_launch_params* params);
 

@@ -28,11 +28,11 @@ import os
 import statistics
 from pathlib import Path
 
-DEFAULT = dict(waves_per_cu=0, fetch_min=16, traverse_min=1, grid_min=8, traverse_steps=3, decide_min=8)
+DEFAULT = dict(waves_per_cu=0, fetch_min=16, traverse_min=16, grid_min=8, traverse_steps=3, decide_min=8)
 SPACE = dict(
     waves_per_cu=[0, 4, 8],
     fetch_min=[4, 8, 16, 24, 32, 48],
-    traverse_min=[1, 2, 8],
+    traverse_min=[1, 8, 16, 24],
     grid_min=[4, 8, 16, 24, 32],
     traverse_steps=[1, 2, 3, 4, 8],
     decide_min=[1, 4, 8, 16, 32],

@@ -100,7 +100,10 @@ struct ccs_scene {
   std::vector<ccs::RefitPass> refit_passes;
   uint32_t* queues = nullptr;  // kQueueSlots ray-queue counters
   std::atomic<uint32_t> next_queue{0};
-  ccs_launch_params launch{0, 16, 1, 8, 3, 8};
+  // traverse_min 16: a walk waits on its chain of loads whatever number of lanes takes
+  // part, so it pays to fill it (460k rays on 200 objects 1.88 -> 1.76 ms against 1, 4.1M
+  // rays on 1M patches 5.33 -> 5.30; at 8, 12, 20 lanes 1.83, 1.83, 1.79)
+  ccs_launch_params launch{0, 16, 16, 8, 3, 8};
   uint2* policy_w = nullptr;   // packed network fragments, allocated on first use
   float4* policy_b = nullptr;
   std::vector<std::pair<void*, size_t>> allocations;  // device buffers and their sizes

@@ -352,7 +352,9 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
 
     __builtin_amdgcn_s_setprio(2);
     // ------------------------------------------- traverse to the next candidate
-    if (mt != 0 && ((uint32_t)__popcll(mt) >= lp.traverse_min || (mc | ms | mg) == 0)) {
+    // once the queue is empty any walking lane starts it, as for the grid phase below
+    const uint32_t traverse_min = drained ? 1u : lp.traverse_min;
+    if (mt != 0 && ((uint32_t)__popcll(mt) >= traverse_min || (mc | ms | mg) == 0)) {
       // at most traverse_steps node visits per phase: lanes still walking keep their
       // place and continue next time, so one lane's long walk does not hold the wave
       for (uint32_t it = 0; mode == kTraverse && cur >= 0 && it < lp.traverse_steps; ++it) {
