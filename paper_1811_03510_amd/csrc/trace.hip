@@ -481,7 +481,11 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
       const uint32_t hr0 = (uint32_t)lane / 3u, hc = (uint32_t)lane - 3u * hr0;
       const uint32_t hr = hr0 < n_own ? hr0 : 0u;
       // the owner's record, path code, depth and type, read by its helpers
-      const int from = (int)nth_set_bit(mg, hr) * 4;
+      // owner of rank r: its number pushed to lane r (all others push to lane 63, which
+      // no helper reads); a search for the r-th set bit of mg takes 30 instructions more
+      // (2M primary and 2M secondary rays on 1M patches 5.28 -> 5.22 ms)
+      const int owners = __builtin_amdgcn_ds_permute(owner ? (int)(4u * rank) : 252, lane * 4);
+      const int from = __builtin_amdgcn_ds_bpermute((int)(4u * hr), owners);
       const uint64_t rp = reinterpret_cast<uint64_t>(recs + (size_t)rec_idx * kRecFloats);
       const uint32_t dg = (uint32_t)depth | ((pmeta & kGregoryBit) ? 0x100u : 0u);
       const uint32_t h_lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)rp);
