@@ -21,8 +21,7 @@
 // recomputes, the mean is 40): once the queue is empty and a wave holds at most
 // kTailRays of them, it spreads each over 16 lanes and its last one over all 64
 // (trace_group.h); launches of few rays run a wave per ray from the start
-// (k_trace_solo; in the learned order 16 lanes, k_trace_wide_learned).  Bits are the
-// same.
+// (k_trace_solo, k_trace_solo_learned).  Bits are the same.
 //
 // Alg. 3 state per lane (registers only, no stack):
 //   code  interleaved path bits of the current domain; split k (u at even k)
@@ -109,9 +108,10 @@ __device__ __forceinline__ void write_hit(const BatchTable& bt, uint32_t* __rest
 }
 
 // A wave's single ray to its end; every value of r is the same in all groups.
-template <int kStride, typename CodeT>
-__device__ __forceinline__ void solo_loop(GroupRay<CodeT>& r, const GroupLane& ln, const BatchTable& bt, int L2,
-                                          float leaf_scale, int lane, int* stack) {
+template <int kStride, bool kLearned, typename CodeT>
+__device__ __forceinline__ void solo_loop(GroupRay<CodeT>& r, const GroupLane& ln, const BatchTable& bt,
+                                          const PolicyDev& policy, uint32_t* feats, int L2, float leaf_scale, int lane,
+                                          int* stack) {
   int cur = uniform(r.cur), sp = uniform(r.sp);  // sp < 0: the ray is done
   for (float* x : {&r.ox, &r.oy, &r.oz, &r.dx, &r.dy, &r.dz, &r.tmin}) *x = uniform(*x);
   r.nodes = uniform(r.nodes);
@@ -140,7 +140,12 @@ __device__ __forceinline__ void solo_loop(GroupRay<CodeT>& r, const GroupLane& l
       }
       cur = first1 ? c1 : c0;
     }
-    if (found) solo_patch(r, ln, L2, leaf_scale, lane);
+    if (found) {
+      if constexpr (kLearned)
+        solo_patch_learned(r, ln, policy, feats, L2, leaf_scale, lane);
+      else
+        solo_patch(r, ln, L2, leaf_scale, lane);
+    }
     if (--sp >= 0) cur = uniform(stack[sp * kStride]);
     walk = true;
   }
@@ -169,12 +174,12 @@ __device__ __forceinline__ void group_loop(GroupRay<CodeT>& r, const GroupLane& 
     if (want != 0) next(want);
     const uint64_t live = __ballot(r.mode != kGroupDead);
     if (live == 0) break;
-    if (!kLearned && __popcll(live) == kGroupLanes && __ballot(r.mode == kGroupFree) == 0) {
+    if (__popcll(live) == kGroupLanes && __ballot(r.mode == kGroupFree) == 0) {
       // the wave's last ray: all groups carry it
       const int owner = __ffsll((unsigned long long)live) - 1;
       spread(r, owner, lane);
       const int at = __shfl((int)(stack - base), owner);
-      solo_loop<kStride>(r, ln, bt, L2, leaf_scale, lane, base + at);
+      solo_loop<kStride, kLearned>(r, ln, bt, policy, feats, L2, leaf_scale, lane, base + at);
       break;
     }
     if (r.mode == kGroupWalk) {
@@ -812,9 +817,8 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
 // against 175 us on 16 lanes and 354 us on one.
 // 1024 primary rays of the torus: 270 -> 76 us; 8192 / 16384 secondary ones: 635 / 621
 // -> 160 / 242 us.
-template <typename CodeT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSoloWaves))) void k_trace_solo(
-    DeviceScene s, BatchTable bt) {
+template <bool kLearned, typename CodeT>
+__device__ __forceinline__ void solo_body(const DeviceScene& s, const BatchTable& bt, uint32_t* feats) {
   __shared__ int stack[kMaxBvhDepth];
   const int lane = threadIdx.x;
   const GroupLane ln(lane);
@@ -827,55 +831,24 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSoloWav
   r.hu = r.hv = 0.0f;
   r.cur = 0;
   r.sp = ray_traced(ro, rd) && s.n_nodes > 0 ? 0 : -1;
+  r.vpref = 0;
   r.mode = kGroupWalk;
-  solo_loop<1>(r, ln, bt, 2 * s.leaf_depth, __uint_as_float((uint32_t)(127 - s.leaf_depth) << 23), lane, stack);
+  solo_loop<1, kLearned>(r, ln, bt, s.policy, feats, 2 * s.leaf_depth,
+                         __uint_as_float((uint32_t)(127 - s.leaf_depth) << 23), lane, stack);
 }
 
-// Small launches in the learned order: every ray on 16 lanes from the start, `groups`
-// (1, 2 or 4) rays to a wave, all of them in flight at once.  16384 torus rays:
-// 797 -> 381 us.
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_trace_wide_learned(
-    DeviceScene s, BatchTable bt, uint32_t groups) {
-  __shared__ int stack[kMaxBvhDepth * kGroupsPerWave];
-  // 16 words per slot of the network's first column tile, of which the groups use four
+template <typename CodeT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSoloWaves))) void k_trace_solo(
+    DeviceScene s, BatchTable bt) {
+  solo_body<false, CodeT>(s, bt, nullptr);
+}
+
+// In the learned order 8192 / 16384 / 40000 secondary rays of the torus: 393 / 398 / 690 ->
+// 341 / 365 / 513 us (on 16 and, the last, on one lane a ray).
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSoloWaves))) void k_trace_solo_learned(
+    DeviceScene s, BatchTable bt) {
   __shared__ __align__(16) uint32_t s_feat[16 * 16];
-  const int lane = threadIdx.x;
-  const uint32_t n = bt.prefix[bt.n_batches];
-  const int L2 = 2 * s.leaf_depth;
-  const float leaf_scale = __uint_as_float((uint32_t)(127 - s.leaf_depth) << 23);
-  const GroupLane ln(lane);
-  const uint32_t group = (uint32_t)lane / kGroupLanes;
-  GroupRay<uint32_t> r;
-  r.rid = blockIdx.x * groups + group;
-  r.mode = group < groups && r.rid < n ? kGroupFree : kGroupDead;
-  bool first = true;
-  int* column = stack + group;
-  group_loop<kGroupsPerWave, true>(r, ln, bt, s.policy, s_feat, L2, leaf_scale, lane, stack, column, [&](uint64_t) {
-    const bool open = first;
-    first = false;
-    if (r.mode != kGroupFree) return;
-    if (!open) {
-      r.mode = kGroupDead;
-      return;
-    }
-    float4 ro, rd;
-    group_open_ray(r, ln, s, bt, ro, rd);
-    r.best_t = rd.w;
-    r.best_id = kNoHit;
-    r.hu = r.hv = 0.0f;
-    r.cur = 0;
-    r.sp = 0;
-    r.vpref = 0;
-    if (ray_traced(ro, rd) && s.n_nodes > 0) {
-      r.mode = kGroupWalk;
-    } else {
-      if ((lane & (kGroupLanes - 1)) == 0) {
-        const Counts none = {0, 0, 0, 0, 0, 0, 0, 0};
-        write_hit<false>(bt, nullptr, r.rid, r.best_t, r.best_id, 0.0f, 0.0f, none);
-      }
-      r.mode = kGroupDead;
-    }
-  });
+  solo_body<true, uint32_t>(s, bt, s_feat);
 }
 
 template <bool kStats, bool kLearned>
@@ -1019,15 +992,6 @@ int max_waves_per_cu(bool counted, bool learned, bool single_box, bool deep) {
   return counted ? resident_waves_per_cu<true, false, false, false>() : resident_waves_per_cu<false, false, false, false>();
 }
 
-static int wide_waves_per_cu() {
-  static const int per_cu = [] {
-    int v = 0;
-    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k_trace_wide_learned, kBlock, 0);
-    return std::max(1, v);
-  }();
-  return per_cu;
-}
-
 // Launches of at most this many rays per compute unit (24576 on 256) take a wave per
 // ray.  Per-ray work is several times the one-lane kernel's, so it loses once the
 // machine is full: 16384 / 24576 / 30000 / 50000 secondary rays of the torus take 242 /
@@ -1035,8 +999,9 @@ static int wide_waves_per_cu() {
 // 262 / 367 / 412 / 622 against 428 / 458 / 457 / 497 us, and in world frames 574 /
 // 961 / 1037 / 1192 against 844 / 1067 / 1139 / 1164 us.
 constexpr uint32_t kSoloRaysPerCu = 96;
-// The learned order's 16-lane kernel: 16384 torus rays 381 us, 20000 on one lane each 680 us.
-constexpr uint32_t kWideRaysPerCu = 64;
+// The learned order costs more a ray on one lane too: 40,000 secondary rays of the torus
+// 513 us against 615, of 200 objects 812 against 828, but 50,000 of those 850 against 842.
+constexpr uint32_t kSoloLearnedRaysPerCu = 160;
 
 // Fewest lanes of a wave that take rays in a launch that all lanes could hold at
 // once, and the waves per compute unit over which it is spread before lanes are
@@ -1065,13 +1030,9 @@ hipError_t launch_intersect(const DeviceScene& s, const BatchTable& bt, uint32_t
       hipLaunchKernelGGL(k_trace_solo<uint32_t>, dim3(n), block, 0, stream, s, bt);
     return hipGetLastError();
   }
-  if (!counters && learned && n <= kWideRaysPerCu * s.n_cus) {
-    const uint32_t room = std::min(limit, (uint32_t)wide_waves_per_cu() * s.n_cus);
-    if (n <= kGroupsPerWave * room) {
-      const uint32_t groups = n <= room ? 1u : n <= 2u * room ? 2u : 4u;
-      hipLaunchKernelGGL(k_trace_wide_learned, dim3((n + groups - 1) / groups), block, 0, stream, s, bt, groups);
-      return hipGetLastError();
-    }
+  if (!counters && learned && n <= std::min(limit, kSoloLearnedRaysPerCu * s.n_cus)) {
+    hipLaunchKernelGGL(k_trace_solo_learned, dim3(n), block, 0, stream, s, bt);
+    return hipGetLastError();
   }
   // rays that all fit are taken by position, without the queue (the learned variant, at its
   // register limit, keeps the queue)

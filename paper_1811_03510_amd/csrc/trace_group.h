@@ -603,6 +603,92 @@ __device__ __forceinline__ void solo_patch(GroupRay<CodeT>& r, const GroupLane& 
   }
 }
 
+// The same in the learned order, a node at a time: the next node depends on the
+// network's answer.  feats: 16 words for each of the 16 columns of a network tile, of
+// which the ray takes the first.
+template <typename CodeT>
+__device__ __forceinline__ void solo_patch_learned(GroupRay<CodeT>& r, const GroupLane& ln, const PolicyDev& policy,
+                                                   uint32_t* feats, int L2, float leaf_scale, int lane) {
+  CodeT trail = uniform(r.trail);
+  CodeT node = uniform(r.code) | (CodeT)1 << (L2 - 1 - uniform(r.depth));
+  bool due = uniform(r.mode) == kGroupGrid;
+  uint32_t vpref = uniform(r.vpref);
+  r.vpref = 0;
+  const int axis = uniform(r.depth) & 1;
+  uint32_t m0 = (uniform(r.mirror) >> axis) & 1u, m1 = (uniform(r.mirror) >> (axis ^ 1)) & 1u;
+  const bool gregory = (uniform(r.pmeta) & kGregoryBit) != 0;
+  for (;;) {
+    if (due) {
+      solo_domain(r, node, L2, leaf_scale);
+      if (gregory)
+        group_grid<2>(r, ln);
+      else
+        group_grid<0>(r, ln);
+      m0 = m1 = 0;
+    }
+    const GroupSplit h = group_split(r);
+    const bool mir = m0 != 0;
+    const bool h_lo = mir ? h.hit_b : h.hit_a, h_up = mir ? h.hit_a : h.hit_b;
+    const float t_lo = mir ? h.tb : h.ta, t_up = mir ? h.ta : h.tb;
+    const bool closer_up = h_up && (!h_lo || t_up < t_lo);
+    int see = uniform((h_lo ? 1 : 0) | (h_up ? 2 : 0) | (closer_up ? 4 : 0));
+    const CodeT bit = lowest(node);
+    const bool along_u = (bit & (CodeT)0x5555555555555555ull) == 0, both = (see & 3) == 3;
+    if ((vpref & 1u) && !along_u && both && bit != 1) see = 3 | (int)((vpref & 2u) << 1);
+    vpref = 0;
+    if ((see & 3) != 0) {
+      if (bit != 1) {
+        const bool decide = along_u && both;
+        if (decide && lane < kGroupLanes) {  // as in group_step
+          if (ln.b0 == ln.b1) {
+            float* o = reinterpret_cast<float*>(feats) + 4 * ln.c + (ln.b0 ? 2 : 0);
+            o[0] = h.e.v[0];
+            o[1] = h.e.v[6];
+          }
+          reinterpret_cast<float4*>(feats)[3] = make_float4(h.ta, h.xa, h.tb, h.xb);
+        }
+        const uint32_t mirror0 = m0 | (m1 << 1);
+        const bool second = ((see >> 2) & 1) != (int)m0;
+        r.g[0] = second ? h.e.v[6] : h.e.v[0];
+        r.g[1] = second ? h.e.v[5] : h.e.v[1];
+        r.g[2] = second ? h.e.v[4] : h.e.v[2];
+        r.g[3] = h.e.v[3];
+        quad_transpose(r.g, ln.b0, ln.b1);
+        const uint32_t m = m0 ^ (second ? 1u : 0u);
+        m0 = m1;
+        m1 = m;
+        trail |= both ? bit : (CodeT)0;
+        node = ((see & 4) ? node : (CodeT)(node ^ bit)) | (CodeT)(bit >> 1);
+        due = gregory;
+        if (decide) {
+          const int k = sizeof(CodeT) == 8 ? __builtin_ctzll((uint64_t)bit) : __builtin_ctz((uint32_t)bit);
+          const float fd = r.frames ? __builtin_amdgcn_rcpf(r.pi) : 0.0f;
+          const float px = __shfl(r.po, 0), py = __shfl(r.po, 4), pz = __shfl(r.po, 8);
+          const float fx = __shfl(fd, 0), fy = __shfl(fd, 4), fz = __shfl(fd, 8);
+          float f[16];
+          policy_features(policy_load_node(feats, 0, mirror0), px, py, pz, r.frames ? fx : r.dx, r.frames ? fy : r.dy,
+                          r.frames ? fz : r.dz, L2 - 1 - k, L2 / 2, gregory, f);
+          policy_store_inputs<16>(feats, 0, f);
+          policy_wave<16>(policy, feats, 1ull, lane);
+          const float4 lg = reinterpret_cast<const float4*>(feats)[0];
+          const uint32_t top = uniform(policy_top(lg.x, lg.y, lg.z, lg.w));
+          vpref = 1u | ((top & 1u) << 1);
+          if ((int)(top >> 1) != ((see >> 2) & 1)) {
+            node ^= bit;  // the other u-half first; the trail bit keeps the closest-first one pending
+            due = true;
+          }
+        }
+        continue;
+      }
+      group_leaf(r, r.pt0 + ((see & 4) ? t_up : t_lo), (CodeT)((node ^ bit) | ((see & 4) ? 1 : 0)), leaf_scale);
+    }
+    if (trail == 0) return;
+    node = pending(node, trail);
+    trail &= trail - 1;
+    due = true;
+  }
+}
+
 // Every group's lanes take the words of the lanes of the group that starts at `first`.
 template <typename T>
 __device__ __forceinline__ void spread(T& x, int first, int lane) {
