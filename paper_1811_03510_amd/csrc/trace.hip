@@ -547,7 +547,11 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
     if (kLearned) {
       const uint64_t md = __ballot(mode == kDecide);
       const uint32_t n_dec = (uint32_t)__popcll(md);
-      if (md != 0 && (few || n_dec >= lp.decide_min || __ballot(mode == kStep) == 0)) {
+      // two lanes are enough once the queue is empty, as for the grid phase (260k rays on 200
+      // objects 1068 -> 1020 us, 131,072 secondary ones 1091 -> 1059; at 1 lane 1050, 1083,
+      // at 4 1015, 1049)
+      const uint32_t decide_min = drained && lp.decide_min > 2u ? 2u : lp.decide_min;
+      if (md != 0 && (few || n_dec >= decide_min || __ballot(mode == kStep) == 0)) {
         // deciding lanes take consecutive slots, so the network runs on ceil(n / 16)
         // column tiles instead of every tile holding one of them (all slot reads of
         // the node values precede the first input store in the wave's program order)
