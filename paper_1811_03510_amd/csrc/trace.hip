@@ -319,7 +319,7 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
       } else {
         const int leader = __ffsll((unsigned long long)mf) - 1;
         if (lane == leader) base = atomicAdd(lp.queue, (uint32_t)__popcll(mf));
-        base = __shfl(base, leader);
+        base = (uint32_t)__builtin_amdgcn_readlane((int)base, leader);
         drained = base + (uint32_t)__popcll(mf) >= n;
       }
       if (mode == kFetch) {
