@@ -142,8 +142,8 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out);
 /* Moves the control points of an existing scene (animation playback, the use
  * case named in the abstract).  Same n, same tags, same layout as at creation.
  * Anchors stay at their creation values.  On the GPU: anchored points and patch
- * boxes are recomputed, then the BVH node boxes level by level from the deepest
- * (one launch per level); the topology is unchanged.  Asynchronous on `stream`;
+ * boxes are recomputed, then the BVH node boxes above them bottom-up, a subtree to a
+ * workgroup (two to four launches); the topology is unchanged.  Asynchronous on `stream`;
  * device input must be 16-byte aligned and stay valid until the stream passes
  * this call.  Host input is staged in a per-scene device buffer and the call
  * returns when the refit is done (synchronous).
@@ -215,7 +215,8 @@ ccs_status ccs_intersect_counted(const ccs_scene* scene, const ccs_ray* rays, ui
  * recomputations; a wave runs the fetch, traversal or recompute phase only when
  * at least the given number of its 64 lanes waits for it (or nothing else can
  * run), so that these divergent phases run on filled waves.  Once every ray has
- * been taken, the traversal phase runs for any lane and the recompute phase for two. */
+ * been taken, the traversal phase runs for any lane, the recompute and network
+ * phases for two. */
 typedef struct ccs_launch_params {
   uint32_t waves_per_cu;   /* resident waves per compute unit; 0 = as many as fit */
   uint32_t fetch_min;      /* 1..64 lanes waiting for a new ray */
