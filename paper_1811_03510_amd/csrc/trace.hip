@@ -328,6 +328,12 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
         if (rid >= n) {
           mode = kDead;
         } else {
+          // From the queue the launch's last rays are taken first: where batches of several
+          // kinds go together, callers put camera rays before the rays that follow from them,
+          // and the heavier rays should not start last (231,401 + 231,401 rays on 200 objects
+          // in world frames 1.79 -> 1.70 ms, 2M + 2M on 1M patches 5.19 -> 5.07, 16 frames of
+          // both 1010 -> 975 us; listed the other way round they lose as much; one kind +-1 %).
+          if (lp.queue != nullptr) rid = n - 1u - rid;
           const ccs_ray* rays = bt.rays[0];
           uint32_t local = rid, frame = bt.frame[0];
           for (uint32_t q = 1; q < bt.n_batches; ++q)
