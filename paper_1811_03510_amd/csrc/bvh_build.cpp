@@ -11,7 +11,8 @@
 #include <cmath>
 #include <cstring>
 #include <limits>
-#include <thread>
+
+#include "beside.h"
 
 namespace ccs {
 namespace {
@@ -173,22 +174,17 @@ struct Builder {
         rb = build(m, e, right_node, depth + 1, &dr);
       }
     };
-    bool spawned = false;
-    std::thread th;
+    bool spare = false;  // a thread for the left child
     if (e - b >= kParallelMin) {
-      int left = __atomic_fetch_sub(&threads_left, 1, __ATOMIC_SEQ_CST);
-      if (left > 1) {
-        th = std::thread(do_left);
-        spawned = true;
-      } else {
-        __atomic_fetch_add(&threads_left, 1, __ATOMIC_SEQ_CST);
-      }
+      spare = __atomic_fetch_sub(&threads_left, 1, __ATOMIC_SEQ_CST) > 1;
+      if (!spare) __atomic_fetch_add(&threads_left, 1, __ATOMIC_SEQ_CST);
     }
-    if (!spawned) do_left();
-    do_right();
-    if (spawned) {
-      th.join();
+    if (spare) {
+      beside(do_left, do_right);
       __atomic_fetch_add(&threads_left, 1, __ATOMIC_SEQ_CST);
+    } else {
+      do_left();
+      do_right();
     }
     set_child(node, 0, lb, m - b == 1 ? ~(int32_t)b : (int32_t)left_node);
     set_child(node, 1, rb, e - m == 1 ? ~(int32_t)m : (int32_t)right_node);

@@ -9,15 +9,17 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <utility>
+#include <exception>
+#include <memory>
 #include <string>
 #include <thread>
+#include <utility>
 #include <vector>
 
 #include "../../include/ccs.h"
-#include "bvh_build.h"
 #include "ccs_internal.h"
 #include "patch_math.h"
+#include "scene_host.h"
 
 namespace {
 
@@ -116,6 +118,7 @@ ccs_status dev_alloc(ccs_scene* s, T** p, size_t count) {
   *p = nullptr;
   const size_t bytes = std::max<size_t>(1, count) * sizeof(T);
   void* q = nullptr;
+  s->allocations.reserve(s->allocations.size() + 1);  // what could throw, before the memory is there
   ccs_status st = raw_alloc(&q, bytes);
   if (st != CCS_OK) return st;
   s->allocations.emplace_back(q, bytes);
@@ -239,10 +242,7 @@ extern "C" {
 
 const char* ccs_last_error(void) { return g_error.c_str(); }
 
-ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
-  g_error.clear();
-  if (!out) return fail(CCS_ERR_INVALID_ARG, "out is NULL");
-  *out = nullptr;
+static ccs_status create_scene(const ccs_scene_desc* desc, ccs_scene** out) {
   if (!desc) return fail(CCS_ERR_INVALID_ARG, "desc is NULL");
   const uint32_t n = desc->n_patches;
   if (n > 0 && (!desc->control_points || !desc->patch_types))
@@ -281,68 +281,17 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
   }
 
   const auto t0 = std::chrono::steady_clock::now();
-  // patch boxes (hull of 16 or 20 points) and fp32 anchors (box centres)
-  std::vector<ccs::BuildBox> boxes(n);
-  for (uint32_t k = 0; k < n; ++k) {
-    const float* p = cp.data() + 60 * (size_t)k;
-    const int np = types[k] == CCS_GREGORY ? 20 : 16;
-    ccs::BuildBox& b = boxes[k];
-    for (int a = 0; a < 3; ++a) b.lo[a] = b.hi[a] = p[a];
-    for (int s = 1; s < np; ++s)
-      for (int a = 0; a < 3; ++a) {
-        b.lo[a] = std::fmin(b.lo[a], p[3 * s + a]);
-        b.hi[a] = std::fmax(b.hi[a], p[3 * s + a]);
-      }
-  }
-  uint32_t log2n = 0;
-  while ((1ull << log2n) < (uint64_t)std::max<uint32_t>(n, 1)) ++log2n;
-  const uint32_t sah_depth = (uint32_t)std::max<int>(8, kTraversalStack - 1 - (int)log2n);
   const int threads = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-  ccs::BvhOutput bvh = ccs::build_bvh(boxes, sah_depth, threads);
+  const ccs::HostScene host = ccs::make_host_scene(cp, types, (uint32_t)kTraversalStack, threads, ccs::kRefitCap0,
+                                                   ccs::kRefitCap1);
+  const ccs::BvhOutput& bvh = host.bvh;
+  const ccs::RefitPlan& plan = host.plan;
   if (n > 0 && bvh.max_depth >= (uint32_t)kTraversalStack)
     return fail(CCS_ERR_UNSUPPORTED, "BVH deeper than the traversal stack");
-
-  // the refit's plan, of a large scene beside the records (26 ms for 1M patches)
-  ccs::RefitPlan plan;
-  auto make_plan = [&]() {
-    plan = ccs::plan_refit(bvh.nodes, bvh.leaf_parent, bvh.node_parent, ccs::kRefitCap0, ccs::kRefitCap1);
-  };
-  std::thread planner;
-  if (n >= (1u << 15))
-    planner = std::thread(make_plan);
-  else
-    make_plan();
-  // records in leaf order
-  std::vector<float> recs((size_t)n * ccs::kRecFloats, 0.0f);
-  std::vector<uint32_t> inv_perm(n);
-  ccs_scene* s = new ccs_scene();
-  for (int a = 0; a < 3; ++a) {
-    s->lo[a] = n ? INFINITY : 0.0f;
-    s->hi[a] = n ? -INFINITY : 0.0f;
-  }
-  for (uint32_t r = 0; r < n; ++r) {
-    const uint32_t k = bvh.perm[r];
-    inv_perm[k] = r;
-    const float* p = cp.data() + 60 * (size_t)k;
-    float* q = recs.data() + (size_t)r * ccs::kRecFloats;
-    const ccs::BuildBox& b = boxes[k];
-    float anc[3];
-    for (int a = 0; a < 3; ++a) {
-      anc[a] = 0.5f * (b.lo[a] + b.hi[a]);
-      s->lo[a] = std::fmin(s->lo[a], b.lo[a]);
-      s->hi[a] = std::fmax(s->hi[a], b.hi[a]);
-    }
-    for (int sl = 0; sl < 16; ++sl)
-      for (int a = 0; a < 3; ++a) q[16 * a + sl] = p[3 * sl + a] - anc[a];
-    for (int sl = 16; sl < 20; ++sl)
-      for (int a = 0; a < 3; ++a) q[48 + 4 * a + (sl - 16)] = p[3 * sl + a] - anc[a];
-    q[60] = anc[0];
-    q[61] = anc[1];
-    q[62] = anc[2];
-    uint32_t meta = k | (types[k] == CCS_GREGORY ? ccs::kGregoryBit : 0u);
-    std::memcpy(q + 63, &meta, 4);
-  }
-  if (planner.joinable()) planner.join();
+  std::unique_ptr<ccs_scene, void (*)(ccs_scene*)> owner(new ccs_scene(), free_scene);
+  ccs_scene* s = owner.get();
+  std::copy(host.lo, host.lo + 3, s->lo);
+  std::copy(host.hi, host.hi + 3, s->hi);
   s->build_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   s->device = dev;
   s->bvh_depth = bvh.max_depth;
@@ -357,7 +306,7 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
   int32_t *lpar = nullptr, *npar = nullptr, *iup = nullptr, *islot = nullptr, *nup = nullptr;
   s->refit_passes = plan.passes;
   float* drec = nullptr;
-  if ((st = dev_alloc(s, &nodes, (size_t)n_nodes * 4)) != CCS_OK || (st = dev_alloc(s, &drec, recs.size())) != CCS_OK ||
+  if ((st = dev_alloc(s, &nodes, (size_t)n_nodes * 4)) != CCS_OK || (st = dev_alloc(s, &drec, host.recs.size())) != CCS_OK ||
       (st = dev_alloc(s, &perm, n)) != CCS_OK || (st = dev_alloc(s, &invp, n)) != CCS_OK ||
       (st = dev_alloc(s, &lpar, n)) != CCS_OK || (st = dev_alloc(s, &npar, n_nodes)) != CCS_OK ||
       (st = dev_alloc(s, &blk_i, plan.block_items.size())) != CCS_OK ||
@@ -366,19 +315,17 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
       (st = dev_alloc(s, &islot, plan.item_slot.size())) != CCS_OK ||
       (st = dev_alloc(s, &nid, plan.node_id.size())) != CCS_OK ||
       (st = dev_alloc(s, &nup, plan.node_up.size())) != CCS_OK ||
-      (st = dev_alloc(s, &s->queues, kQueueSlots)) != CCS_OK) {
-    free_scene(s);
+      (st = dev_alloc(s, &s->queues, kQueueSlots)) != CCS_OK)
     return st;
-  }
   hipStream_t stream = (hipStream_t)desc->stream;
   struct Up {
     void* dst;
     const void* src;
     size_t bytes;
   } ups[] = {{nodes, bvh.nodes.data(), bvh.nodes.size() * sizeof(float)},
-             {drec, recs.data(), recs.size() * sizeof(float)},
+             {drec, host.recs.data(), host.recs.size() * sizeof(float)},
              {perm, bvh.perm.data(), (size_t)n * 4},
-             {invp, inv_perm.data(), (size_t)n * 4},
+             {invp, host.inv_perm.data(), (size_t)n * 4},
              {lpar, bvh.leaf_parent.data(), (size_t)n * 4},
              {npar, bvh.node_parent.data(), (size_t)n_nodes * 4},
              {blk_i, plan.block_items.data(), plan.block_items.size() * 4},
@@ -390,16 +337,10 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
   for (const Up& u : ups) {
     if (u.bytes == 0) continue;
     e = hipMemcpyAsync(u.dst, u.src, u.bytes, hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess) {
-      free_scene(s);
-      return hip_fail(e, "uploading the scene");
-    }
+    if (e != hipSuccess) return hip_fail(e, "uploading the scene");
   }
   e = hipStreamSynchronize(stream);
-  if (e != hipSuccess) {
-    free_scene(s);
-    return hip_fail(e, "synchronizing the scene upload");
-  }
+  if (e != hipSuccess) return hip_fail(e, "synchronizing the scene upload");
   D.nodes = nodes;
   D.recs = drec;
   D.perm = perm;
@@ -409,10 +350,7 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
   D.refit = ccs::RefitDev{blk_i, blk_n, nid, iup, islot, nup};
   int cus = 0;
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) {
-    free_scene(s);
-    return hip_fail(e, "hipDeviceGetAttribute");
-  }
+  if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");
   D.n_cus = (uint32_t)std::max(1, cus);
   D.n_frames = 1;
   D.frame_rec_floats = (size_t)n * ccs::kRecFloats;
@@ -421,22 +359,24 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
     // frames, and records in them, come from the refit kernel, so that creation and
     // every later refit compute them with the same arithmetic
     D.frame_frames_f4 = (size_t)n * 3;
-    if ((st = dev_alloc(s, &D.frames, D.frame_frames_f4)) != CCS_OK) {
-      free_scene(s);
-      return st;
-    }
-    st = ccs_refit_frame(s, 0, cp.data(), CCS_HOST, desc->stream);
-    if (st == CCS_OK) {
-      e = hipStreamSynchronize(stream);
-      if (e != hipSuccess) st = hip_fail(e, "placing patches in their frames");
-    }
-    if (st != CCS_OK) {
-      free_scene(s);
-      return st;
-    }
+    if ((st = dev_alloc(s, &D.frames, D.frame_frames_f4)) != CCS_OK) return st;
+    if ((st = ccs_refit_frame(s, 0, cp.data(), CCS_HOST, desc->stream)) != CCS_OK) return st;
+    e = hipStreamSynchronize(stream);
+    if (e != hipSuccess) return hip_fail(e, "placing patches in their frames");
   }
-  *out = s;
+  *out = owner.release();
   return CCS_OK;
+}
+
+ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out) {
+  g_error.clear();
+  if (!out) return fail(CCS_ERR_INVALID_ARG, "out is NULL");
+  *out = nullptr;
+  try {
+    return create_scene(desc, out);
+  } catch (const std::exception&) {  // the host build ran out of memory
+    return fail(CCS_ERR_OOM, "no host memory");  // short enough to need none
+  }
 }
 
 ccs_status ccs_scene_set_frames(ccs_scene* s, uint32_t n_frames) {

@@ -17,12 +17,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-namespace ccs {
+#include "record.h"
 
-constexpr int kRecFloats = 64;
-constexpr uint32_t kGregoryBit = 0x80000000u;
-constexpr uint32_t kIdMask = 0x7FFFFFFFu;
-constexpr uint32_t kNoHit = 0xFFFFFFFFu;
+namespace ccs {
 
 struct Grid {
   float x[4][4], y[4][4], z[4][4];
