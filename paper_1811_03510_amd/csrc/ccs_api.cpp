@@ -285,7 +285,6 @@ static ccs_status create_scene(const ccs_scene_desc* desc, ccs_scene** out) {
   const ccs::HostScene host = ccs::make_host_scene(cp, types, (uint32_t)kTraversalStack, threads, ccs::kRefitCap0,
                                                    ccs::kRefitCap1);
   const ccs::BvhOutput& bvh = host.bvh;
-  const ccs::RefitPlan& plan = host.plan;
   if (n > 0 && bvh.max_depth >= (uint32_t)kTraversalStack)
     return fail(CCS_ERR_UNSUPPORTED, "BVH deeper than the traversal stack");
   std::unique_ptr<ccs_scene, void (*)(ccs_scene*)> owner(new ccs_scene(), free_scene);
@@ -293,6 +292,7 @@ static ccs_status create_scene(const ccs_scene_desc* desc, ccs_scene** out) {
   std::copy(host.lo, host.lo + 3, s->lo);
   std::copy(host.hi, host.hi + 3, s->hi);
   s->build_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+  s->refit_passes = host.refit_passes;
   s->device = dev;
   s->bvh_depth = bvh.max_depth;
   const uint32_t n_nodes = n ? (uint32_t)(bvh.nodes.size() / 16) : 0;
@@ -302,19 +302,11 @@ static ccs_status create_scene(const ccs_scene_desc* desc, ccs_scene** out) {
   D.leaf_depth = (int)desc->leaf_depth;
   D.single_box = (desc->flags & CCS_FLAG_SINGLE_BOX) != 0;
   float4* nodes = nullptr;
-  uint32_t *perm = nullptr, *invp = nullptr, *blk_i = nullptr, *blk_n = nullptr, *nid = nullptr;
-  int32_t *lpar = nullptr, *npar = nullptr, *iup = nullptr, *islot = nullptr, *nup = nullptr;
-  s->refit_passes = plan.passes;
+  uint32_t *invp = nullptr, *refit = nullptr;
   float* drec = nullptr;
-  if ((st = dev_alloc(s, &nodes, (size_t)n_nodes * 4)) != CCS_OK || (st = dev_alloc(s, &drec, host.recs.size())) != CCS_OK ||
-      (st = dev_alloc(s, &perm, n)) != CCS_OK || (st = dev_alloc(s, &invp, n)) != CCS_OK ||
-      (st = dev_alloc(s, &lpar, n)) != CCS_OK || (st = dev_alloc(s, &npar, n_nodes)) != CCS_OK ||
-      (st = dev_alloc(s, &blk_i, plan.block_items.size())) != CCS_OK ||
-      (st = dev_alloc(s, &blk_n, plan.block_nodes.size())) != CCS_OK ||
-      (st = dev_alloc(s, &iup, plan.item_up.size())) != CCS_OK ||
-      (st = dev_alloc(s, &islot, plan.item_slot.size())) != CCS_OK ||
-      (st = dev_alloc(s, &nid, plan.node_id.size())) != CCS_OK ||
-      (st = dev_alloc(s, &nup, plan.node_up.size())) != CCS_OK ||
+  if ((st = dev_alloc(s, &nodes, (size_t)n_nodes * 4)) != CCS_OK ||
+      (st = dev_alloc(s, &drec, host.recs.size())) != CCS_OK || (st = dev_alloc(s, &invp, n)) != CCS_OK ||
+      (st = dev_alloc(s, &refit, host.refit.words.size())) != CCS_OK ||
       (st = dev_alloc(s, &s->queues, kQueueSlots)) != CCS_OK)
     return st;
   hipStream_t stream = (hipStream_t)desc->stream;
@@ -324,16 +316,8 @@ static ccs_status create_scene(const ccs_scene_desc* desc, ccs_scene** out) {
     size_t bytes;
   } ups[] = {{nodes, bvh.nodes.data(), bvh.nodes.size() * sizeof(float)},
              {drec, host.recs.data(), host.recs.size() * sizeof(float)},
-             {perm, bvh.perm.data(), (size_t)n * 4},
              {invp, host.inv_perm.data(), (size_t)n * 4},
-             {lpar, bvh.leaf_parent.data(), (size_t)n * 4},
-             {npar, bvh.node_parent.data(), (size_t)n_nodes * 4},
-             {blk_i, plan.block_items.data(), plan.block_items.size() * 4},
-             {blk_n, plan.block_nodes.data(), plan.block_nodes.size() * 4},
-             {iup, plan.item_up.data(), plan.item_up.size() * 4},
-             {islot, plan.item_slot.data(), plan.item_slot.size() * 4},
-             {nid, plan.node_id.data(), plan.node_id.size() * 4},
-             {nup, plan.node_up.data(), plan.node_up.size() * 4}};
+             {refit, host.refit.words.data(), host.refit.words.size() * 4}};
   for (const Up& u : ups) {
     if (u.bytes == 0) continue;
     e = hipMemcpyAsync(u.dst, u.src, u.bytes, hipMemcpyHostToDevice, stream);
@@ -343,11 +327,14 @@ static ccs_status create_scene(const ccs_scene_desc* desc, ccs_scene** out) {
   if (e != hipSuccess) return hip_fail(e, "synchronizing the scene upload");
   D.nodes = nodes;
   D.recs = drec;
-  D.perm = perm;
   D.inv_perm = invp;
-  D.leaf_parent = lpar;
-  D.node_parent = npar;
-  D.refit = ccs::RefitDev{blk_i, blk_n, nid, iup, islot, nup};
+  const ccs::RefitWords& w = host.refit;
+  D.refit.block_items = w.one_block ? nullptr : refit + w.block_items;
+  D.refit.block_nodes = w.one_block ? nullptr : refit + w.block_nodes;
+  D.refit.node_id = refit + w.node_id;
+  D.refit.node_up = reinterpret_cast<const int32_t*>(refit + w.node_up);
+  D.refit.item_up = reinterpret_cast<const int32_t*>(refit + w.item_up);
+  D.refit.item_slot = reinterpret_cast<const int32_t*>(refit + w.item_slot);
   int cus = 0;
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return hip_fail(e, "hipDeviceGetAttribute");

@@ -19,7 +19,8 @@ struct PolicyDev {
   const float4* b;  // kPolicyBTiles * 64 lanes x 4 fp32
 };
 
-// The refit plan's arrays on the device (refit_plan.h).
+// The refit plan's arrays on the device (RefitWords in refit_plan.h); a plan of one block
+// has no block_items and block_nodes.
 struct RefitDev {
   const uint32_t *block_items, *block_nodes, *node_id;
   const int32_t *item_up, *item_slot, *node_up;
@@ -39,10 +40,7 @@ struct DeviceScene {
   uint32_t n_patches;
   uint32_t n_nodes;
   int leaf_depth;
-  const uint32_t* perm;      // record -> original index
   const uint32_t* inv_perm;  // original index -> record
-  const int32_t* leaf_parent;  // record -> (node << 1 | side)
-  const int32_t* node_parent;  // node -> (parent << 1 | side), -1 for the root
   RefitDev refit;              // the refit's work plan (refit_plan.h)
   uint32_t n_cus;            // compute units of the device
   uint32_t n_frames;         // frames: copies of recs and node boxes sharing one topology

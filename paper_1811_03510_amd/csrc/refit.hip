@@ -14,7 +14,7 @@
 // written back at kernel end).  A launch per BVH level instead spent 2 to 5 us on
 // each level: refits of 512, 200,000 and 1,000,000 patches take 10.3, 47 and 212 us
 // against 27.5 (11 launches), 93.5 (26) and 294 us.  What bounds them now is a chain
-// of latencies per workgroup (its item range, perm, points, stores, climb): without
+// of latencies per workgroup (its item range, the records' last words, points, stores, climb): without
 // the stores 200,000 patches take 41 us, without the climb 41, with the points in
 // record order 45; with the frame in each of a patch's lanes, 48.
 // With patch-local frames the per-patch pass also recomputes each patch's frame and
@@ -57,8 +57,7 @@ struct Treelets {
   }
 
   // From an item whose box is (lo, hi) and whose parent in the block is `link`.
-  __device__ __forceinline__ void climb(float4* nodes, const int32_t* __restrict__ node_parent, int32_t link,
-                                        float lo[3], float hi[3]) {
+  __device__ __forceinline__ void climb(float4* nodes, int32_t link, float lo[3], float hi[3]) {
     while (true) {
       const uint32_t k = (uint32_t)link >> 1;
       float* own = box[k] + ((link & 1) ? 6 : 0);
@@ -84,8 +83,7 @@ struct Treelets {
       hi[2] = fmaxf(y.y, z.w);
       link = up[k];
       if (link < 0) {  // a treelet's root: its box goes to its slot, for the next pass
-        const int32_t slot = node_parent[id[k]];
-        if (slot >= 0) write_child_box(nodes, slot >> 1, slot & 1, lo, hi);
+        if (link != kRefitTop) write_child_box(nodes, ~link >> 1, ~link & 1, lo, hi);
         return;
       }
     }
@@ -147,13 +145,19 @@ __device__ __forceinline__ void patch_rows(const float p00[3], const float p30[3
 __global__ __launch_bounds__(kRefitBlock) void k_refit_patches(DeviceScene s, const float* __restrict__ cp) {
   __shared__ __align__(16) Treelets<kRefitCap0> tree;
   __shared__ float rows[kRefitCap0][9];
-  const uint32_t first = s.refit.block_items[blockIdx.x], end = s.refit.block_items[blockIdx.x + 1];
-  const uint32_t nodes0 = s.refit.block_nodes[blockIdx.x];
-  tree.load(s.refit, nodes0, s.refit.block_nodes[blockIdx.x + 1] - nodes0);
+  uint32_t first = 0, end = s.n_patches, nodes0 = 0, nodes1 = s.n_nodes;
+  if (s.refit.block_items) {
+    first = s.refit.block_items[blockIdx.x];
+    end = s.refit.block_items[blockIdx.x + 1];
+    nodes0 = s.refit.block_nodes[blockIdx.x];
+    nodes1 = s.refit.block_nodes[blockIdx.x + 1];
+  }
+  tree.load(s.refit, nodes0, nodes1 - nodes0);
   // the frames' rows, a lane per patch of the first wave (their roots and divisions
   // in each of a patch's four lanes would double the kernel's instructions)
   if (s.frames && threadIdx.x < kRefitCap0 && first + threadIdx.x < end) {
-    const float* src = cp + (size_t)s.perm[first + threadIdx.x] * 60;
+    const uint32_t meta = __float_as_uint(s.recs[(size_t)(first + threadIdx.x) * kRecFloats + 63]);
+    const float* src = cp + (size_t)(meta & kIdMask) * 60;
     patch_rows(src, src + 9, src + 36, rows[threadIdx.x]);
   }
   __syncthreads();
@@ -163,7 +167,7 @@ __global__ __launch_bounds__(kRefitBlock) void k_refit_patches(DeviceScene s, co
   float* rec = s.recs + (size_t)r * kRecFloats;
   const float4 meta = reinterpret_cast<const float4*>(rec)[15];  // anchor xyz, meta bits: unchanged
   const bool greg = (__float_as_uint(meta.w) & kGregoryBit) != 0;
-  const float* src = cp + (size_t)s.perm[r] * 60;  // 240 B, 16-B aligned
+  const float* src = cp + (size_t)(__float_as_uint(meta.w) & kIdMask) * 60;  // 240 B, 16-B aligned
   float p[5][3];                                   // grid points 4j .. 4j + 3, then P^v point 16 + j
   {
     const float4* g = reinterpret_cast<const float4*>(src) + 3 * j;
@@ -235,15 +239,13 @@ __global__ __launch_bounds__(kRefitBlock) void k_refit_patches(DeviceScene s, co
     write_child_box(nodes, 0, 0, lo, hi);
     write_child_box(nodes, 0, 1, lo, hi);
   } else if (up < 0) {
-    const int32_t slot = s.leaf_parent[r];
-    write_child_box(nodes, slot >> 1, slot & 1, lo, hi);
+    write_child_box(nodes, ~up >> 1, ~up & 1, lo, hi);
   } else {
-    tree.climb(nodes, s.node_parent, up, lo, hi);
+    tree.climb(nodes, up, lo, hi);
   }
 }
 
-__global__ __launch_bounds__(kRefitCap1) void k_refit_boxes(float4* __restrict__ nodes,
-                                                            const int32_t* __restrict__ node_parent, RefitDev plan,
+__global__ __launch_bounds__(kRefitCap1) void k_refit_boxes(float4* __restrict__ nodes, RefitDev plan,
                                                             uint32_t first_block, uint32_t n_records) {
   __shared__ __align__(16) Treelets<kRefitCap1> tree;
   const uint32_t block = first_block + blockIdx.x;
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(kRefitCap1) void k_refit_boxes(float4* __restrict__
   const int32_t slot = plan.item_slot[k - n_records];
   const float* f = reinterpret_cast<const float*>(nodes + 4 * (size_t)(slot >> 1)) + ((slot & 1) ? 6 : 0);
   float lo[3] = {f[0], f[1], f[2]}, hi[3] = {f[3], f[4], f[5]};
-  tree.climb(nodes, node_parent, plan.item_up[k], lo, hi);
+  tree.climb(nodes, plan.item_up[k], lo, hi);
 }
 
 hipError_t launch_refit(const DeviceScene& s, const float* cp_world, const std::vector<RefitPass>& passes,
@@ -267,7 +269,7 @@ hipError_t launch_refit(const DeviceScene& s, const float* cp_world, const std::
       hipLaunchKernelGGL(k_refit_patches, grid, dim3(kRefitBlock), 0, stream, s, cp_world);
     else
       hipLaunchKernelGGL(k_refit_boxes, grid, dim3(kRefitCap1), 0, stream, const_cast<float4*>(s.nodes),
-                         s.node_parent, s.refit, passes[k].first_block, s.n_patches);
+                         s.refit, passes[k].first_block, s.n_patches);
   }
   return hipGetLastError();
 }

@@ -1,5 +1,6 @@
 #include "refit_plan.h"
 
+#include <cstddef>
 #include <cstring>
 #include <utility>
 
@@ -107,6 +108,33 @@ RefitPlan plan_refit(const std::vector<float>& nodes, const std::vector<int32_t>
     for (const int32_t s : next) item[(size_t)s] = 1;  // what lies below them is not looked at again
   }
   return plan;
+}
+
+RefitWords refit_words(const RefitPlan& plan, const std::vector<int32_t>& leaf_parent,
+                       const std::vector<int32_t>& node_parent) {
+  RefitWords r;
+  r.one_block = plan.passes.size() <= 1 && (plan.passes.empty() || plan.passes[0].n_blocks == 1);
+  const size_t table = r.one_block ? 0 : plan.block_items.size();
+  r.words.reserve(2 * table + plan.item_up.size() + plan.item_slot.size() + 2 * plan.node_id.size());
+  auto put = [&](const auto& v, size_t count) {
+    const size_t at = r.words.size();
+    r.words.insert(r.words.end(), v.begin(), v.begin() + (std::ptrdiff_t)count);
+    return at;
+  };
+  r.block_items = put(plan.block_items, table);
+  r.block_nodes = put(plan.block_nodes, table);
+  r.node_id = put(plan.node_id, plan.node_id.size());
+  r.node_up = put(plan.node_up, plan.node_up.size());
+  r.item_up = put(plan.item_up, plan.item_up.size());
+  r.item_slot = put(plan.item_slot, plan.item_slot.size());
+  for (size_t k = 0; k < plan.node_up.size(); ++k)
+    if (plan.node_up[k] < 0) {
+      const int32_t slot = node_parent[plan.node_id[k]];
+      r.words[r.node_up + k] = (uint32_t)(slot < 0 ? kRefitTop : ~slot);
+    }
+  for (size_t k = 0; k < plan.item_up.size(); ++k)
+    if (plan.item_up[k] < 0) r.words[r.item_up + k] = (uint32_t)~leaf_parent[k];  // a record above every treelet
+  return r;
 }
 
 }  // namespace ccs

@@ -12,6 +12,7 @@
 // the two boxes and goes on, the first one stops.
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -32,6 +33,21 @@ struct RefitPlan {
   std::vector<uint32_t> node_id;      // node of a block -> node of the BVH
   std::vector<int32_t> node_up;       // node of a block -> link to its parent in the block, -1: a treelet's root
 };
+
+// The plan as the device reads it, one array of words.  A link that leaves its block is
+// the slot it goes to, as ~slot, so that the device needs no parents of nodes and records
+// besides (with them a scene held more memory than with a list of nodes by depth):
+// 12 bytes a patch, 8 a treelet and 8 a block.  A single block needs no table:
+// it holds every record and every node, in order.
+constexpr int32_t kRefitTop = INT32_MIN;  // in node_up: the root of the BVH
+struct RefitWords {
+  std::vector<uint32_t> words;
+  bool one_block = true;
+  size_t block_items = 0, block_nodes = 0, node_id = 0, node_up = 0, item_up = 0, item_slot = 0;  // where each begins
+};
+
+RefitWords refit_words(const RefitPlan& plan, const std::vector<int32_t>& leaf_parent,
+                       const std::vector<int32_t>& node_parent);
 
 // nodes: 16 floats per node, the children's references as bits at 12 and 13 (>= 0
 // node, < 0 record ~child), in depth-first order (left child = node + 1); leaf_parent

@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <utility>
 
 #include "../../include/ccs.h"
 #include "beside.h"
@@ -64,7 +65,11 @@ HostScene make_host_scene(const std::vector<float>& cp, const std::vector<uint8_
       std::memcpy(q + 63, &meta, 4);
     }
   };
-  auto plan = [&]() { s.plan = plan_refit(s.bvh.nodes, s.bvh.leaf_parent, s.bvh.node_parent, refit_cap0, refit_cap1); };
+  auto plan = [&]() {
+    RefitPlan p = plan_refit(s.bvh.nodes, s.bvh.leaf_parent, s.bvh.node_parent, refit_cap0, refit_cap1);
+    s.refit = refit_words(p, s.bvh.leaf_parent, s.bvh.node_parent);
+    s.refit_passes = std::move(p.passes);
+  };
   // of a large scene beside each other (the plan takes 26 ms for 1M patches)
   if (n >= (1u << 15)) {
     beside(plan, records);

@@ -12,9 +12,10 @@ namespace ccs {
 
 struct HostScene {
   BvhOutput bvh;
-  RefitPlan plan;                  // empty, as what follows, when the BVH is too deep
-  std::vector<float> recs;         // kRecFloats per patch, in leaf order, in world frames
-  std::vector<uint32_t> inv_perm;  // input patch index -> record
+  std::vector<RefitPass> refit_passes;  // empty, as what follows, when the BVH is too deep
+  RefitWords refit;
+  std::vector<float> recs;              // kRecFloats per patch, in leaf order, in world frames
+  std::vector<uint32_t> inv_perm;       // input patch index -> record
   float lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};  // scene bounds
 };
 

@@ -78,7 +78,7 @@ int main() {
     }
     auto same = [&](const ccs::HostScene& s) {
       return s.recs == want.recs && s.inv_perm == want.inv_perm && s.bvh.perm == want.bvh.perm &&
-             s.plan.item_up == want.plan.item_up && s.plan.node_up == want.plan.node_up;
+             s.refit.words == want.refit.words;
     };
     const long held = g_live.load();
     long refused = 0;
