@@ -54,19 +54,32 @@ ccs_status device_cap(uint64_t& cap) {
   return CCS_OK;
 }
 
-// Counts `bytes` as held, unless that would exceed the cap.
+ccs_status over_cap(size_t bytes, uint64_t cap, uint64_t held) {
+  return fail(CCS_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes would exceed " +
+                               "CCS_MAX_DEVICE_BYTES=" + std::to_string(cap) + " (" + std::to_string(held) +
+                               " bytes held)");
+}
+
+// Counts `bytes` as held, unless that would exceed the cap.  What is refused is never
+// counted: it would refuse other calls memory that nobody holds.
 ccs_status reserve(size_t bytes) {
   uint64_t cap;
   ccs_status st = device_cap(cap);
   if (st != CCS_OK) return st;
-  const uint64_t before = g_live_bytes.fetch_add(bytes);
-  if (cap != 0 && before + bytes > cap) {
-    g_live_bytes.fetch_sub(bytes);
-    return fail(CCS_ERR_OOM, "device allocation of " + std::to_string(bytes) + " bytes would exceed " +
-                                 "CCS_MAX_DEVICE_BYTES=" + std::to_string(cap) + " (" + std::to_string(before) +
-                                 " bytes held)");
-  }
+  uint64_t held = g_live_bytes.load();
+  do {
+    if (cap != 0 && held + bytes > cap) return over_cap(bytes, cap, held);
+  } while (!g_live_bytes.compare_exchange_weak(held, held + bytes));
   return CCS_OK;
+}
+
+// Refuses what reserve would refuse, and counts nothing.
+ccs_status check_cap(size_t bytes) {
+  uint64_t cap;
+  ccs_status st = device_cap(cap);
+  if (st != CCS_OK) return st;
+  const uint64_t held = g_live_bytes.load();
+  return cap != 0 && held + bytes > cap ? over_cap(bytes, cap, held) : CCS_OK;
 }
 
 // Every device allocation of the library goes through this pair.
@@ -652,12 +665,11 @@ ccs_status ccs_policy_infer(const float* params, const float* features, uint32_t
   g_error.clear();
   if (n == 0) return CCS_OK;
   if (!params || !features || !logits) return fail(CCS_ERR_INVALID_ARG, "a pointer is NULL");
-  // The inference holds no device memory of its own.  Its packed operands used to be a
-  // temporary, and a cap that refused them still refuses the call.
+  // The inference holds no device memory of its own, so nothing is charged.  A cap without
+  // room for the packed operands, which it once kept for the call, still refuses it.
   constexpr size_t kOperands = 64 * (ccs::kPolicyWTiles * sizeof(uint2) + ccs::kPolicyBTiles * sizeof(float4));
-  ccs_status st = reserve(kOperands);
+  ccs_status st = check_cap(kOperands);
   if (st != CCS_OK) return st;
-  g_live_bytes.fetch_sub(kOperands);
   hipStream_t str = (hipStream_t)stream;
   hipError_t e = ccs::launch_policy_infer(params, features, n, logits, str);
   if (e == hipSuccess) e = hipStreamSynchronize(str);
