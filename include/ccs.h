@@ -176,7 +176,12 @@ typedef struct ccs_batch {
  * per-batch tail).  batches is a host array of at most 32 entries, copied into
  * the launch's arguments: it may be freed on return, and the launch can be
  * captured in a HIP graph.  Each hit equals what ccs_intersect gives for that
- * ray on that frame.  Asynchronous on `stream`; at most 2^31 - 1 rays. */
+ * ray on that frame, in whatever order batches and rays are listed; only the time
+ * depends on it.  A launch of more rays than the GPU holds at once starts with the
+ * rays listed last, so the batches whose rays take longest (secondary rays) belong
+ * at the end: camera rays and as many secondary rays in one launch take 2 to 5 %
+ * longer listed the other way round.  Asynchronous on `stream`; at most 2^31 - 1
+ * rays. */
 ccs_status ccs_intersect_batched(const ccs_scene* scene, const ccs_batch* batches, uint32_t n_batches,
                                  void* stream);
 

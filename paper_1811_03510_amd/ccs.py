@@ -203,7 +203,8 @@ class Scene:
                                      _stream(stream)))
 
     def intersect_batched(self, batches, stream=None, counted: bool = False):
-        """batches: list of (frame, rays (N, 8) cuda float32, hits (N, 4) cuda float32 or None).
+        """batches: list of (frame, rays (N, 8) cuda float32, hits (N, 4) cuda float32 or None); those listed last are
+        started first, so the slowest kind (secondary rays) belongs at the end.
         Returns the list of hit tensors (one launch for all batches), and with counted
         also the (sum N, 8) int32 work counters of the launch's rays in batch order."""
         import torch

@@ -328,11 +328,13 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
         if (rid >= n) {
           mode = kDead;
         } else {
-          // From the queue the launch's last rays are taken first: where batches of several
-          // kinds go together, callers put camera rays before the rays that follow from them,
-          // and the heavier rays should not start last (231,401 + 231,401 rays on 200 objects
-          // in world frames 1.79 -> 1.70 ms, 2M + 2M on 1M patches 5.19 -> 5.07, 16 frames of
-          // both 1010 -> 975 us; listed the other way round they lose as much; one kind +-1 %).
+          // From the queue the launch's last rays are taken first, so that a caller can have
+          // the heavier kind started first by listing it last.  It is a rule on the order of
+          // the arguments and favours one listing: the queue read from its front, or its end,
+          // camera rays listed first 1762, 1859 or 1660, 1668 us (231,401 + 231,401 rays on
+          // 200 objects in world frames, two seeds), 5.22, 5.18 or 5.12, 5.05 ms (2M + 2M on
+          // 1M patches); secondary rays listed first 1652, 1770 or 1762, 1703 us, 5.04, 5.00
+          // or 5.29, 5.21 ms.  One kind alone +-1 %.
           if (lp.queue != nullptr) rid = n - 1u - rid;
           const ccs_ray* rays = bt.rays[0];
           uint32_t local = rid, frame = bt.frame[0];
