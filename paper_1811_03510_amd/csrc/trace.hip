@@ -1049,9 +1049,16 @@ hipError_t launch_intersect(const DeviceScene& s, const BatchTable& bt, uint32_t
     hipLaunchKernelGGL(k_trace_solo_learned, dim3(n), block, 0, stream, s, bt);
     return hipGetLastError();
   }
-  // Rays that all fit are taken by position, without the queue.  In the learned order 65,536
-  // secondary rays of the torus take 547 us against 589 from the queue with all lanes
-  // filled, of 200 objects 707 against 837, in world frames 2273 against 2453.
+  // Rays that all fit are taken by position, without the queue.  Against the queue with all
+  // lanes filled, over 18 launches of one torus and fields of 50 to 300 objects in both kinds
+  // of frames (camera and secondary rays half and half), the learned order takes 0.88 of the
+  // time at 65,536 rays, 0.93 at 98,304, 0.95 at 114,688, 1.02 at 131,072, 0.94 at 150,000
+  // and 1.00 at 196,608, where every lane is filled; secondary rays alone 0.92, 0.97, 1.00,
+  // 1.01, 1.01 and 1.09.  Closest first secondary rays alone take 0.93, 0.96, 0.99, 1.02, 0.99
+  // and 1.13.  Above 100,000 rays it depends on the scene and the rays, which no rule on
+  // sizes sees: half and half, the torus gains (150,000 rays closest first 404 us against 470,
+  // in the learned order 0.88 of the time, 0.74 in world frames) and fields in world frames
+  // lose (4 to 11 %).
   uint32_t n_waves = std::min(waves, (n + kBlock - 1) / kBlock);
   if (n <= waves * kBlock) {
     const uint32_t spread = std::min(waves, kSpreadWavesPerCu * s.n_cus);
