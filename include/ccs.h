@@ -143,7 +143,8 @@ ccs_status ccs_scene_create(const ccs_scene_desc* desc, ccs_scene** out);
  * case named in the abstract).  Same n, same tags, same layout as at creation.
  * Anchors stay at their creation values.  On the GPU: anchored points and patch
  * boxes are recomputed, then the BVH node boxes above them bottom-up, a subtree to a
- * workgroup (two to four launches); the topology is unchanged.  Asynchronous on `stream`;
+ * workgroup (one launch for up to 64 patches, two or three for up to millions); the
+ * topology is unchanged.  Asynchronous on `stream`;
  * device input must be 16-byte aligned and stay valid until the stream passes
  * this call.  Host input is staged in a per-scene device buffer and the call
  * returns when the refit is done (synchronous).
@@ -207,9 +208,10 @@ ccs_status ccs_intersect(const ccs_scene* scene, const ccs_ray* rays, uint32_t n
  * splits), backtracks, Gregory bound recomputations (Alg. 2, including each
  * Gregory candidate's root), leaf records, Bezier grid re-crops after
  * backtracking (Alg. 1), Gregory candidates.  A separately compiled copy of the
- * same kernel that keeps every ray on one lane to its end (ccs_intersect spreads
- * the rays of a small launch, and a launch's last ones, over 16 lanes each, with
- * the same hits); used for measurement. */
+ * same kernel that keeps every ray on one lane to its end (ccs_intersect runs a
+ * wave per ray in a small launch, and spreads a launch's last rays over 16 lanes
+ * each and a wave's last one over all 64, with the same hits); used for
+ * measurement. */
 ccs_status ccs_intersect_counted(const ccs_scene* scene, const ccs_ray* rays, uint32_t n, ccs_hit* hits,
                                  uint32_t* counters, void* stream);
 
@@ -401,7 +403,8 @@ ccs_status ccs_scene_info_get(const ccs_scene* scene, ccs_scene_info* info);
  * library holds in this process above the value of the environment variable
  * CCS_MAX_DEVICE_BYTES (a decimal byte count, read at each allocation; unset,
  * empty or 0: no cap; anything else: CCS_ERR_INVALID_ARG).  A call that fails
- * this way frees whatever it had allocated.  ccs_device_bytes_in_use() returns
+ * this way frees whatever it had allocated.  ccs_policy_infer holds nothing, but is
+ * refused where its packed operands (9 KB) would not fit.  ccs_device_bytes_in_use() returns
  * the bytes held right now: the sum of ccs_scene_info.device_bytes over live
  * scenes plus the temporaries of calls in progress.  Thread-safe. */
 uint64_t ccs_device_bytes_in_use(void);

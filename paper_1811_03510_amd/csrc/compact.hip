@@ -21,7 +21,8 @@
 // 184,000 16.3 -> 12.8 us.  1024 or 4096 blocks and 2 or 8 loads in flight are no faster
 // at any size.
 //
-// More rays: one launch (k_compact_tiles, below).
+// More rays: one pass over them (k_compact_tiles, below), after a launch that clears its
+// words.  The sizes at which the forms change are those of 256 CUs.
 
 #include "ccs_internal.h"
 #include "ray_valid.h"
@@ -36,7 +37,7 @@ constexpr int kCompactLoads = 4;           // loads in flight: 32 rays each
 constexpr int kTileWaves = 16, kTileBlock = 64 * kTileWaves;
 constexpr int kTileLoads = 16;  // loads in flight, and halves of rays a lane holds
 constexpr uint32_t kTileRays = 32u * kTileLoads * kTileWaves;  // 8192
-// One launch from the size on at which every CU has more than one tile, up to what the
+// One pass from the size on at which every CU has more than one tile, up to what the
 // 30 bits of a tile's word can count: 4,000,000 rays (30 % active) 60 -> 55 us and
 // 8,294,399 rays 123 -> 100 us, but 921,600 rays 17 -> 21 us.
 constexpr uint32_t kTilesFrom = 256u * kTileRays + 1u, kTilesTo = (1u << 30) - 1u;
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(kCompactBlock) void k_compact_scatter(const ccs_ray
   }
 }
 
-// One launch over tiles of kTileRays consecutive rays, a tile per block, which holds
+// One pass over tiles of kTileRays consecutive rays, a tile per block, which holds
 // its rays in registers while it learns how many active rays lie before them
 // (decoupled look-back, Merrill and Garland 2016), so that every ray is read once.
 // Tiles are taken by a ticket: every tile before a block's own is held by a block that

@@ -10,7 +10,8 @@
 // instructions and the recompute ~220, without a memory access (the record stays in
 // registers): 0.94 us per Gregory level.  With all 64 lanes on one ray, below, it is
 // 0.47 us.  Per ray this issues several times as many instructions, so it is used only
-// where lanes would idle: small launches and the last rays of a wave.
+// where lanes would idle: for the last rays of a wave (a small launch runs a wave per ray
+// from the start).
 //
 // Lane l of a group: b = l & 3, q = l >> 2, component c = min(q, 2) (q = 3 repeats
 // z, so that a reduction over the four quads is one over the three components).
