@@ -249,13 +249,6 @@ template <bool kStats, bool kLearned, bool kSingle, typename CodeT>
 __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTable& bt, uint32_t* __restrict__ counters,
                                            const LaunchParams& lp) {
   constexpr int kStack = kLearned ? (int)kMaxBvhDepthLearned : (int)kMaxBvhDepth;
-  // The kernels that spread a launch's last rays over lanes.  The counting and single-box
-  // kernels do not, so a launch of theirs lasts until its heaviest rays have ended on one
-  // lane each.  Taking the queue from its end, setting candidates up in batches and
-  // splitting twice a turn fill the waves before that and delay those rays: with these and
-  // without, single box 300,000 camera rays of the torus in world frames 4.93 and 4.23 ms,
-  // 1M secondary ones 8.03 and 7.34, 600,000 camera rays of 60 objects in patch frames 2.82
-  // and 2.70; counting 1M secondary rays of the torus in world frames 4.30 and 3.49.
   constexpr bool kTail = !kStats && !kSingle;
   uint64_t busy = 0;      // lanes that hold a ray
   bool drained = false;   // the queue is known to be empty
@@ -342,7 +335,7 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
           // 200 objects in world frames, two seeds), 5.22, 5.18 or 5.12, 5.05 ms (2M + 2M on
           // 1M patches); secondary rays listed first 1652, 1770 or 1762, 1703 us, 5.04, 5.00
           // or 5.29, 5.21 ms.  One kind alone +-1 %.
-          if (kTail && lp.queue != nullptr) rid = n - 1u - rid;
+          if (lp.queue != nullptr) rid = n - 1u - rid;
           const ccs_ray* rays = bt.rays[0];
           uint32_t local = rid, frame = bt.frame[0];
           for (uint32_t q = 1; q < bt.n_batches; ++q)
@@ -426,7 +419,7 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
     // 2M primary and 2M secondary rays on 1M patches 5.92 -> 5.58 ms (at 1, 4, 12 lanes:
     // 5.80, 5.67, 5.60).  Not in world frames, where it is 40 instructions (460k rays on
     // 200 objects 1.85 -> 1.89 ms at 8), and not once the queue is empty (as grid_min).
-    const uint32_t setup_min = kTail && s.frames != nullptr && !drained ? kSetupMin : 1u;
+    const uint32_t setup_min = s.frames != nullptr && !drained ? kSetupMin : 1u;
     if (mc != 0 && ((uint32_t)__popcll(mc) >= setup_min || (ms | mg) == 0)) {
       if (mode == kTraverse && cur < 0) {  // candidate patch: set up Alg. 3 at the root
         if (kStats) cnt.cand++;
@@ -606,7 +599,10 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
     // of 16 frames 970 -> 909 us; at 8 lanes 5.33, up to three or four splits 5.34, 5.32.
     // The learned order splits once: the second copy of the step costs it registers, and
     // many of its lanes wait for the network (2M secondary rays on 200 objects 4.84 -> 4.71
-    // ms, in world frames 12.4 -> 11.7).
+    // ms, in world frames 12.4 -> 11.7).  The single box also does: its launches last as long
+    // as their heaviest rays on one lane each, which wait while others split again (2M + 2M
+    // rays on 1M patches 10.9 -> 10.55 ms; 300,000 and 1M rays on one torus and 60 objects 2
+    // to 3 % less, six seeds).
     for (bool again = false;; again = true) {
       if (mode == kStep) {
         if (kStats) cnt.split++;
@@ -738,7 +734,7 @@ __device__ __forceinline__ void trace_body(const DeviceScene& s, const BatchTabl
           }
         }
       }
-      if (kLearned || !kTail || again || __popcll(__ballot(mode == kStep)) < kSplitAgain) break;
+      if (kLearned || kSingle || again || __popcll(__ballot(mode == kStep)) < kSplitAgain) break;
     }
   }
   // The wave's last rays, 16 lanes each (trace_group.h).  Their states go through
