@@ -12,8 +12,8 @@
 // LDS) unions the boxes and goes on.  Launch boundaries order the passes, so no
 // thread waits on another and no device-wide fence is needed (each XCD's L2 is
 // written back at kernel end).  A launch per BVH level instead spent 2 to 5 us on
-// each level: refits of 512, 200,000 and 1,000,000 patches take 10.3, 47 and 212 us
-// against 27.5 (11 launches), 93.5 (26) and 294 us.  What bounds them now is a chain
+// each level: refits of 512, 200,000 and 1,000,000 patches take 9.8, 45 and 202 us
+// against 27.5 (11 launches), 91 (26) and 287 us.  What bounds them now is a chain
 // of latencies per workgroup (its item range, the records' last words, points, stores, climb): without
 // the stores 200,000 patches take 41 us, without the climb 41, with the points in
 // record order 45; with the frame in each of a patch's lanes, 48.
